@@ -46,8 +46,12 @@ hipError_t launch_gemv_a8_narrow(const cq_weight &w, const int8_t *x8, const flo
 // Model-dtype many-row GEMM for B <= 5 (tensors below 2 GiB).  tile_rows is
 // the x-tile height (32, 64, 128 or 256), 0 for the built-in choice by m.
 bool gemm_a16_mfma_supported(const cq_weight &w, int64_t m);
-int a16_mfma_tile_rows(int64_t m);
 hipError_t launch_gemm_a16_mfma(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
+                                int tile_rows, hipStream_t stream);
+// Its tall tiles, every B and G a power of two from 32 to 512: tile_rows is 64,
+// 128, 160 or 256, 0 for the built-in choice by the shape.
+bool gemm_a16_wide_supported(const cq_weight &w, int64_t m);
+hipError_t launch_gemm_a16_wide(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
                                 int tile_rows, hipStream_t stream);
 // The same GEMM with the decoded weight rounded once to the activation dtype
 // (one MFMA per product for BF16; FP16 is the default kernel).

@@ -17,11 +17,10 @@
 //
 // Tiling.  A workgroup owns a TM x TN tile of y (rows of x by rows of W);
 // each of its waves owns a block of 16 x 16 MFMA tiles of it and issues
-// v_mfma_f32_16x16x32_{bf16,f16}.  Many rows of x take 256 x 128 tiles (8
-// waves of 64 x 64), so every decoded weight feeds 256 rows; few rows take
-// tiles of 128, 64 or 32 rows, so no matrix work is spent on absent rows and
-// the narrower weight tiles of the shorter ones put more workgroups on the
-// chip.  K advances one 32-code unit per step through two LDS buffers; while
+// v_mfma_f32_16x16x32_{bf16,f16}.  Up to 64 rows of x take tiles of 64 or 32
+// rows, whose narrow weight tiles put many workgroups on the chip; more rows
+// are the work of gemm_a16_wide.h, and the 256 x 128 tile (8 waves of 64 x 64)
+// here serves the single-rounded operand only.  K advances one 32-code unit per step through two LDS buffers; while
 // the matrix cores work on one, every thread decodes its codes of the next
 // step into the other, so one barrier per step suffices.  Code words,
 // activations and group metadata of a step are requested R steps ahead into
@@ -106,9 +105,8 @@ struct a16_tile {
     static constexpr int NT = 64 * WM * WN;
     static constexpr int TM = 16 * BI * WM, TN = 16 * BJ * WN;
 };
-// x-tile height 256 (many rows), 128, 64 and 32 (few rows)
+// x-tile height 256 (the single-rounded operand), 64 and 32 (few rows)
 using tile256 = a16_tile<4, 2, 4, 4, 2>;
-using tile128 = a16_tile<2, 4, 4, 2, 8>;
 using tile64 = a16_tile<1, 4, 4, 1, 8>;
 using tile32 = a16_tile<1, 4, 2, 1, 8>;
 
@@ -414,8 +412,6 @@ hipError_t launch_a16_tile32(const cq_weight &w, const void *x, int x_dt, int64_
                              hipStream_t stream);
 hipError_t launch_a16_tile64(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool one,
                              hipStream_t stream);
-hipError_t launch_a16_tile128(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool one,
-                              hipStream_t stream);
 hipError_t launch_a16_tile256(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool one,
                               hipStream_t stream);
 

@@ -6,8 +6,7 @@ namespace cq {
 
 hipError_t launch_a16_tile256(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool one,
                              hipStream_t stream) {
-    return one ? a16_mfma_dtypes<true, tile256>(w, x, x_dt, m, y, y_dt, stream)
-               : a16_mfma_dtypes<false, tile256>(w, x, x_dt, m, y, y_dt, stream);
+    return one ? a16_mfma_dtypes<true, tile256>(w, x, x_dt, m, y, y_dt, stream) : hipErrorNotSupported;
 }
 
 }  // namespace cq

@@ -1,0 +1,91 @@
+"""GPU parity of the lane-decoded matrix-core GEMMs over every payload width.
+
+Weights are random codes (the reserved pattern among them) with random scales
+and admissible shapes; the bounds are elementwise and follow from the operand
+formats, so that one wrong code, scale or row fails.
+"""
+import numpy as np
+import pytest
+
+from oracle import format as F
+from tests._cases import act, say
+from workloads import PRINTED_SHAPES, to_f16_bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
+    import paper_2608_06763_amd as cq
+    cq.lib()
+    return torch
+
+
+def random_weight(seed, n, k, bits, group, repeat=1):
+    """(CQWeight of n * repeat rows, codes, scale, a, b of the n rows); a few
+    fields hold the reserved pattern, whose code is given as 0."""
+    import torch
+    import paper_2608_06763_amd as cq
+    g = np.random.Generator(np.random.PCG64(seed))
+    m = F.max_code(bits)
+    codes = g.integers(-m, m + 1, (n, k)) if bits > 1 else g.integers(0, 2, (n, k)) * 2 - 1
+    fields = np.mod(codes, 1 << bits) if bits > 1 else (codes > 0).astype(np.int64)
+    if bits > 1:
+        reserved = g.random((n, k)) < 0.01
+        fields[reserved] = 1 << (bits - 1)
+        codes[reserved] = 0
+    stream = ((fields[:, :, None] >> np.arange(bits)) & 1).astype(np.uint8).reshape(n, k * bits)
+    packed = np.packbits(stream, axis=1, bitorder="little")
+    ng = k // group
+    scale = (0.02 * np.exp(0.5 * g.standard_normal((n, ng)))).astype(np.float32)
+    shapes = np.array(PRINTED_SHAPES)[g.integers(0, len(PRINTED_SHAPES), (n, ng))]
+    a, b = to_f16_bits(shapes[..., 0]), to_f16_bits(shapes[..., 1])
+    rep = lambda v, dt: torch.from_numpy(np.ascontiguousarray(v).view(dt)).cuda().repeat(repeat, 1)
+    w = cq.CQWeight(rep(packed, np.uint8), rep(scale, np.float32), rep(a, np.int16), rep(b, np.int16), bits, group,
+                    n * repeat, k)
+    return w, codes, scale, a, b
+
+
+def model_dtype_bound(xv, wd, dtype):
+    """Largest error of sum x w with the weight as hi + lo BF16 parts (hi and lo
+    each rounded once, at most 2^-18 of the weight, and an FP32 level within
+    2^-20) or as one FP16 operand (2^-11), plus the FP32 accumulation over K."""
+    per_weight = 2.0 ** -17 if dtype == "bf16" else 2.0 ** -11 + 2.0 ** -20
+    mass = np.abs(xv) @ np.abs(wd).T
+    return (per_weight + 2.0 ** -24 * np.sqrt(xv.shape[1]) * 4) * mass + 1e-30
+
+
+# m: one row block, a ragged tile of 64, 128 and (with many weight rows, where
+# the built-in height changes) 160 and 256 rows of x; K: several loop trips, an
+# odd number of steps, an odd number of 32-code units where the width allows it
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("group,k", [(32, 1152), (64, 1152), (128, 1152), (256, 1280), (512, 1536)])
+@pytest.mark.parametrize("m,repeat", [(17, 1), (130, 1), (300, 104), (450, 104)])
+def test_wide_model_dtype(torch_dev, bits, group, k, m, repeat):
+    import paper_2608_06763_amd as cq
+    if group == 32 and bits in (4, 8):
+        k = 1056
+    if repeat > 1 and group not in (32, 128):
+        pytest.skip("tall tiles are covered at two group sizes")
+    n = 131
+    w, codes, scale, a, b = random_weight(900 + bits, n, k, bits, group, repeat)
+    wd = F.decode(codes, bits, group, scale, a, b)
+    # up to five bits the fixed heights, above them the conservative family
+    families = ("gemm_mfma", "gemm_mfma_m128", "gemm_mfma_m256") if bits <= 5 else ("gemm_tiled",)
+    for dtype in ("bf16", "fp16"):
+        xb, xv = act(901 + m, m, k, dtype)
+        x = torch_dev.from_numpy(xb.view(np.int16)).cuda().view(
+            torch_dev.bfloat16 if dtype == "bf16" else torch_dev.float16)
+        want, bound = xv @ wd.T, model_dtype_bound(xv, wd, dtype)
+        for f in families:
+            say("wide", bits, group, k, m, repeat, dtype, f)
+            y = cq.cq_gemm_model_dtype_family(w, x, f, y_dtype=torch_dev.float32)
+            assert torch_dev.equal(y, cq.cq_gemm_model_dtype_family(w, x, f, y_dtype=torch_dev.float32))
+            got = y.view(m, repeat, n)
+            assert torch_dev.equal(got[:, -1], got[:, 0])
+            got = got[:, 0].cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(got - want) <= bound), f
+            y16 = cq.cq_gemm_model_dtype_family(w, x, f)
+            assert torch_dev.equal(y16, y.to(y16.dtype)), f
