@@ -310,9 +310,9 @@ int64_t cq_get_gemv_max_rows(int32_t path);
  *   GEMV_GENERIC  conservative one-wave-per-row GEMV (m <= 16, every B, G)
  *   GEMM_MFMA     tiled matrix-core GEMM (model dtype B <= 5; A8 W3/W4 with
  *                 G >= 64)
- *   GEMM_TILED    conservative tiled GEMM (every B, G): 64 x 64 tiles; model
- *                 dtype B >= 6 runs the wide lane-decoded kernel where its
- *                 32-bit offsets reach
+ *   GEMM_TILED    conservative tiled GEMM (every B, G): 64 x 64 tiles; A8
+ *                 without a partials dump and model dtype B >= 6 run the wide
+ *                 lane-decoded kernels where their 32-bit offsets reach
  *   GEMM_MFMA_ROUNDED  model dtype only: the tiled matrix-core GEMM with the
  *                 decoded weight s_g q rounded once to the activation dtype
  *                 before the dot, the dense rounding point of Sec. 5.3 (BF16:
@@ -324,9 +324,8 @@ int64_t cq_get_gemv_max_rows(int32_t path);
  *                 caller's selection table may.
  *   GEMM_MFMA_M32, _M64, _M128, _M256  GEMM_MFMA with a fixed x-tile height
  *                 (rows of x per workgroup tile; the tile-height dimension of
- *                 the selection in Sec. 5.6).  A8 GEMM_MFMA picks the smallest of
- *                 32, 64, 128 that holds m, else 256, the model dtype 32 or 64
- *                 up to 64 rows and above that by the shape (an A8 partials dump
+ *                 the selection in Sec. 5.6).  GEMM_MFMA picks 32 or 64 up to 64
+ *                 rows and above that by the shape (an A8 partials dump
  *                 always runs the 256-row tile).  Same widths as GEMM_MFMA.
  *   GEMM_SLAB     model dtype only, 1 <= m <= 32, B <= 5: matrix-core GEMM for
  *                 few rows in which every lane decodes its codes straight into

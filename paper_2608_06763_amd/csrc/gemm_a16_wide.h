@@ -32,6 +32,7 @@
 #include "cq_device.h"
 #include "cq_internal.h"
 #include "stream_common.h"
+#include "wide_common.h"
 
 #include <type_traits>
 
@@ -61,14 +62,6 @@ __device__ __forceinline__ f32x4_t mma(const u32x4 &a, const u32x4 &b, f32x4_t c
                                                       c, 0, 0, 0);
 }
 
-template <int P0, int PN, typename F>
-__device__ __forceinline__ void unroll(F &&f) {
-    if constexpr (P0 < PN) {
-        f(std::integral_constant<int, P0>{});
-        unroll<P0 + 1, PN>(f);
-    }
-}
-
 __device__ __forceinline__ uint32_t pack_bf16(float v0, float v1) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{v0, v1}, bf16x2_t));
 }
@@ -79,31 +72,6 @@ __device__ __forceinline__ uint32_t pack_f16(float v0, float v1) {
 
 __device__ __forceinline__ uint32_t bperm(uint32_t hi, uint32_t lo, uint32_t sel) {
     return __builtin_amdgcn_perm(hi, lo, sel);
-}
-
-// Every lane brings 16 bytes from its byte offset voff (+ soff) to LDS bytes
-// dst + 16 lane .. +15 (dst wave-uniform), without passing through registers.
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, uint8_t *dst, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, voff, soff, 0, 0);
-}
-
-// Keep loads in program order across this point, for the compiler (the kernel's
-// pointers carry no __restrict__, so that a load cannot be moved over the empty
-// asm) and for its scheduler.
-__device__ __forceinline__ void vmem_order() {
-    __asm__ volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0x78f);
-}
-
-// Wait until at most N vector-memory loads are in flight and every LDS read
-// has returned.
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-    static_assert(N >= 0 && N < 64, "counter range");
-    __asm__ volatile("" ::: "memory");
-    // vmcnt in bits 3:0 and 15:14, expcnt (no wait) 6:4, lgkmcnt 11:8
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);
-    __asm__ volatile("" ::: "memory");
 }
 
 // hi and lo operand words of two FP32 weights (hi = RNE(v), lo = RNE(v - hi));
@@ -354,11 +322,7 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
         else return xs3;
     };
 
-    // workgroups of one XCD (blockIdx modulo 8) take consecutive tiles, which
-    // walk the weight tiles of one activation tile
-    const int nwg = tiles_m * tiles_n;
-    const int xcd = int(blockIdx.x) & 7, per = nwg >> 3, rem = nwg & 7;
-    const int wg = xcd * per + min(xcd, rem) + (int(blockIdx.x) >> 3);
+    const int wg = xcd_tile(tiles_m * tiles_n);
     const int m0 = (wg / tiles_n) * TM;
     const int n0 = (wg % tiles_n) * kTN;
 

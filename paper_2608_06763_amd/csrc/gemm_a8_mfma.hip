@@ -1,4 +1,6 @@
-// Dynamic-A8 many-row GEMM (Sec. 5.4) for W4 on gfx950 int8 matrix cores.
+// Dynamic-A8 many-row GEMM (Sec. 5.4) for W4 with the INT32 partials dump, on
+// gfx950 int8 matrix cores, and the choice among the many-row kernels (without
+// a dump: gemm_a8_tile.hip up to 64 rows, else gemm_a8_wide.h).
 //
 // Numerics are eq. a8-output: INT8 activations times exact INT8 weight
 // carriers (eq. carrier) accumulate into exact INT32 group partials P_g
@@ -448,29 +450,16 @@ static hipError_t a8_mfma_launch(const cq_weight &w, const int8_t *x8, const flo
     return hipGetLastError();
 }
 
-template <int B, int YDT, bool TB>
-static hipError_t a8_mfma_group(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y,
-                                int32_t *partials, const int8_t *ctab, hipStream_t stream) {
-    // The partials dump (a test path) runs four waves per workgroup, which
-    // leaves room for its extra registers; the fast path runs eight.
-    if (partials) {
-        if constexpr (B != 4) {
-            return hipErrorNotSupported;  // W3 partials: the 64x64 kernel
-        } else {
-        switch (w.group) {
-            case 64: return a8_mfma_launch<B, 2, 2, 2, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
-            case 128: return a8_mfma_launch<B, 2, 2, 4, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
-            case 256: return a8_mfma_launch<B, 2, 2, 8, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
-            case 512: return a8_mfma_launch<B, 2, 2, 16, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
-        }
-        return hipErrorNotSupported;
-        }
-    }
+// The partials dump runs four waves per workgroup, which leaves room for its
+// extra registers.
+template <int YDT>
+static hipError_t a8_mfma_dump(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y,
+                               int32_t *partials, hipStream_t stream) {
     switch (w.group) {
-        case 64: return a8_mfma_launch<B, 4, 2, 2, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
-        case 128: return a8_mfma_launch<B, 4, 2, 4, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
-        case 256: return a8_mfma_launch<B, 4, 2, 8, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
-        case 512: return a8_mfma_launch<B, 4, 2, 16, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
+        case 64: return a8_mfma_launch<4, 2, 2, 2, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
+        case 128: return a8_mfma_launch<4, 2, 2, 4, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
+        case 256: return a8_mfma_launch<4, 2, 2, 8, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
+        case 512: return a8_mfma_launch<4, 2, 2, 16, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
     }
     return hipErrorNotSupported;
 }
@@ -481,36 +470,28 @@ bool gemm_a8_mfma_supported(const cq_weight &w, int64_t m) {
            stream_fits(w.n, w.k, w.bits, w.group) && w.n < lim && m < lim;
 }
 
-template <bool TB>
-static hipError_t a8_mfma_dispatch(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx,
-                                   int64_t m, void *y, int y_dt, int32_t *partials, hipStream_t stream) {
-    if (w.bits == 3) {
-        if (y_dt == 0) return a8_mfma_group<3, 0, TB>(w, x8, dx, m, y, partials, ctab, stream);
-        if (y_dt == 1) return a8_mfma_group<3, 1, TB>(w, x8, dx, m, y, partials, ctab, stream);
-        return a8_mfma_group<3, 2, TB>(w, x8, dx, m, y, partials, ctab, stream);
-    }
-    if (y_dt == 0) return a8_mfma_group<4, 0, TB>(w, x8, dx, m, y, partials, ctab, stream);
-    if (y_dt == 1) return a8_mfma_group<4, 1, TB>(w, x8, dx, m, y, partials, ctab, stream);
-    return a8_mfma_group<4, 2, TB>(w, x8, dx, m, y, partials, ctab, stream);
-}
-
-// x-tile height for m rows when the caller does not name one: the smallest
-// of 32, 64, 128 that holds m (gemm_a8_tile.hip), else 256 (this file)
-static int a8_mfma_tile_rows(int64_t m) { return m <= 32 ? 32 : m <= 64 ? 64 : m <= 128 ? 128 : 256; }
+// x-tile height for m rows when the caller does not name one: up to 64 rows
+// the split-K tiles of gemm_a8_tile.hip, else the wide kernel (0: its choice)
+static int a8_mfma_tile_rows(int64_t m) { return m <= 32 ? 32 : m <= 64 ? 64 : 0; }
 
 hipError_t launch_gemm_a8_mfma(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y, int y_dt,
                                int32_t *partials, int tile_rows, hipStream_t stream) {
-    // the partials dump is written by the 256-row kernel's four-wave variant
-    const int tr = partials ? 256 : (tile_rows ? tile_rows : a8_mfma_tile_rows(m));
-    if (tr != 256) return launch_gemm_a8_tile(w, nullptr, x8, dx, m, y, y_dt, tr, stream);
-    return a8_mfma_dispatch<false>(w, nullptr, x8, dx, m, y, y_dt, partials, stream);
+    if (partials) {
+        if (w.bits != 4) return hipErrorNotSupported;  // W3 partials: the 64 x 64 kernel
+        if (y_dt == 0) return a8_mfma_dump<0>(w, x8, dx, m, y, partials, stream);
+        if (y_dt == 1) return a8_mfma_dump<1>(w, x8, dx, m, y, partials, stream);
+        return a8_mfma_dump<2>(w, x8, dx, m, y, partials, stream);
+    }
+    const int tr = tile_rows ? tile_rows : a8_mfma_tile_rows(m);
+    if (tr == 32 || tr == 64) return launch_gemm_a8_tile(w, nullptr, x8, dx, m, y, y_dt, tr, stream);
+    return launch_gemm_a8_wide(w, nullptr, x8, dx, m, y, y_dt, tr, stream);
 }
 
 hipError_t launch_gemm_a8_mfma_tab(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx,
                                    int64_t m, void *y, int y_dt, hipStream_t stream) {
     const int tr = a8_mfma_tile_rows(m);
-    if (tr != 256) return launch_gemm_a8_tile(w, ctab, x8, dx, m, y, y_dt, tr, stream);
-    return a8_mfma_dispatch<true>(w, ctab, x8, dx, m, y, y_dt, nullptr, stream);
+    if (tr) return launch_gemm_a8_tile(w, ctab, x8, dx, m, y, y_dt, tr, stream);
+    return launch_gemm_a8_wide(w, ctab, x8, dx, m, y, y_dt, 0, stream);
 }
 
 }  // namespace cq

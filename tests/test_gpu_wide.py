@@ -89,3 +89,70 @@ def test_wide_model_dtype(torch_dev, bits, group, k, m, repeat):
             assert np.all(np.abs(got - want) <= bound), f
             y16 = cq.cq_gemm_model_dtype_family(w, x, f)
             assert torch_dev.equal(y16, y.to(y16.dtype)), f
+
+
+# A8: the wide kernel against the conservative one (whose partials dump keeps
+# it) bit for bit, both rescale the exact INT32 partials in group order, and
+# against the oracle's semantics.  Heights of 32 to 256 rows, K ending inside a
+# step for the smaller groups, G above and below a step.
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("group,k", [(32, 1152), (64, 1152), (64, 1216), (128, 1152), (256, 1280), (512, 1536)])
+@pytest.mark.parametrize("m,repeat", [(17, 1), (130, 1), (500, 104)])
+def test_wide_a8(torch_dev, bits, group, k, m, repeat):
+    import paper_2608_06763_amd as cq
+    from oracle import a8 as A8
+    if group == 32 and bits in (4, 8):
+        k = 1056  # an odd number of units
+    if (k * bits) % 128:
+        pytest.skip("rows must be whole 16-byte units")
+    if repeat > 1 and group == 256:
+        pytest.skip("one long-group size at the tall tiles")
+    n = 131
+    w, codes, scale, a, b = random_weight(950 + bits, n, k, bits, group, repeat)
+    xb, xv = act(951 + m, m, k)
+    x8_np, dx_np = A8.quantize_act(xv)
+    x8, dx = torch_dev.from_numpy(x8_np).cuda(), torch_dev.from_numpy(dx_np.astype(np.float32)).cuda()
+    families = ("gemm_tiled",)
+    if bits in (3, 4) and group >= 64:
+        families = ("gemm_tiled", "gemm_mfma_m128", "gemm_mfma_m256") + (("gemm_mfma",) if m > 64 else ())
+    base, _ = cq.cq_gemm_a8(w, x8, dx, y_dtype=torch_dev.float32, want_partials=True) if m * n * repeat < 1 << 20 \
+        else (None, None)
+    ref = None
+    if repeat == 1:
+        ref, _ = A8.gemm_a8(x8_np, dx_np, codes, bits, group, scale, a, b)
+    for f in families:
+        say("wide a8", bits, group, k, m, repeat, f)
+        y = cq.cq_gemm_a8_family(w, x8, dx, f, y_dtype=torch_dev.float32)
+        assert torch_dev.equal(y, cq.cq_gemm_a8_family(w, x8, dx, f, y_dtype=torch_dev.float32)), f
+        if base is not None:
+            assert torch_dev.equal(y, base), f
+        if repeat > 1:
+            got = y.view(m, repeat, n)
+            one = cq.CQWeight(w.codes[:n], w.scale[:n], w.a[:n], w.b[:n], bits, group, n, k)
+            small, _ = cq.cq_gemm_a8(one, x8, dx, y_dtype=torch_dev.float32, want_partials=True)
+            assert torch_dev.equal(got[:, 0], small) and torch_dev.equal(got[:, -1], small), f
+        else:
+            assert np.max(np.abs(y.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref)), f
+        for dt in (torch_dev.bfloat16, torch_dev.float16):
+            assert torch_dev.equal(cq.cq_gemm_a8_family(w, x8, dx, f, y_dtype=dt), y.to(dt)), f
+
+
+# rows whose shapes put a carrier within 3e-4 of a half-integer: exact integer
+# sums from every kernel that forms carriers
+@pytest.mark.parametrize("bits", range(3, 9))
+@pytest.mark.parametrize("group", [32, 64, 128, 256])
+def test_wide_a8_near_ties(torch_dev, bits, group):
+    import paper_2608_06763_amd as cq
+    from tests._cases import carrier_probe
+    if (2 * group * bits) % 128:
+        pytest.skip("rows must be whole 16-byte units")
+    codes, s, a, b, x8, dx, p = carrier_probe(bits, group)
+    w = cq.CQWeight.from_codes(codes, s, a, b, bits, group)
+    m = 70
+    x8_t = torch_dev.from_numpy(np.repeat(x8, m, axis=0)).cuda()
+    dx_t = torch_dev.from_numpy(np.repeat(dx, m)).cuda()
+    want = np.repeat(p.sum(axis=-1).astype(np.float64).reshape(1, -1), m, axis=0)
+    for f in ("gemm_tiled",) + (("gemm_mfma_m128",) if bits <= 4 and group >= 64 else ()):
+        say("wide near ties", bits, group, f)
+        y = cq.cq_gemm_a8_family(w, x8_t, dx_t, f, y_dtype=torch_dev.float32).cpu().numpy().astype(np.float64)
+        assert np.array_equal(y, want), f
