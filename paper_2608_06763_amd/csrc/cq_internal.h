@@ -53,6 +53,12 @@ hipError_t launch_gemm_a16_mfma(const cq_weight &w, const void *x, int x_dt, int
 bool gemm_a16_wide_supported(const cq_weight &w, int64_t m);
 hipError_t launch_gemm_a16_wide(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
                                 int tile_rows, hipStream_t stream);
+// Few rows with split K (gemm_a16_split.h); whole: FP32 weights in three operand
+// parts, m <= 16 and B >= 6.
+bool gemm_a16_split_whole_preferred(const cq_weight &w, int64_t m);
+bool gemm_a16_split_preferred(const cq_weight &w, int64_t m);
+hipError_t launch_gemm_a16_split(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool whole,
+                                 hipStream_t stream);
 // The same GEMM with the decoded weight rounded once to the activation dtype
 // (one MFMA per product for BF16; FP16 is the default kernel).
 hipError_t launch_gemm_a16_mfma_rounded(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,

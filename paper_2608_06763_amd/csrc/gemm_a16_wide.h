@@ -134,6 +134,7 @@ template <int B, int XDT>
 struct curve_decoder {
     float s, a, b, c;
 
+    template <bool SHARE = true>
     __device__ __forceinline__ void build(float sv, uint32_t a16, uint32_t b16, int q) {
         const float av = f16_to_f32(uint16_t(a16)), bv = f16_to_f32(uint16_t(b16));
         const float cv = 1.f - av - bv;
@@ -196,6 +197,9 @@ struct table_decoder {
     static constexpr int NW = B >= 3 ? 2 : 1;
     uint32_t ta[NP][NW];
 
+    // SHARE: the four lanes of a row (q = 0..3) form the tables of one group
+    // together; without it every lane forms its own
+    template <bool SHARE = true>
     __device__ __forceinline__ void build(float s, uint32_t a16, uint32_t b16, int q) {
         if constexpr (B <= 2) {
             uint32_t h, l;
@@ -228,6 +232,15 @@ struct table_decoder {
                     ta[p][1] = bperm(t, t, 0x0102030cu) ^ (p & 1 ? 0x80808000u : 0u);  // 0, -3, -2, -1
                 }
             } else {
+                if constexpr (!SHARE) {
+                    uint32_t h[4], l[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        split2<XDT>(lev(float(2 * i) / float(M)), lev(float(2 * i + 1) / float(M)), h[i], l[i]);
+                    planes(h, 0);
+                    if constexpr (NP == 4) planes(l, 2);
+                    return;
+                }
                 // the lanes l % 16 + 16 q of a row evaluate magnitudes 2q, 2q + 1
                 // and share them by row swaps
                 const float t0 = float(2 * q) / float(M), t1 = float(2 * q + 1) / float(M);
@@ -244,11 +257,15 @@ struct table_decoder {
         const auto s32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);  // lanes 0..31, lanes 32..63
         const auto s0 = __builtin_amdgcn_permlane16_swap(s32[0], s32[0], false, false);
         const auto s1 = __builtin_amdgcn_permlane16_swap(s32[1], s32[1], false, false);
+        const uint32_t v[4] = {s0[0], s0[1], s1[0], s1[1]};
+        planes(v, p);
+    }
+    __device__ __forceinline__ void planes(const uint32_t *v, int p) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const uint32_t sel = e ? 0x07050301u : 0x06040200u;
-            ta[p + e][0] = bperm(s0[1], s0[0], sel);
-            ta[p + e][NW - 1] = bperm(s1[1], s1[0], sel);
+            ta[p + e][0] = bperm(v[1], v[0], sel);
+            ta[p + e][NW - 1] = bperm(v[3], v[2], sel);
         }
     }
     // operand words of the lane's eight codes, four codes at a time
@@ -335,7 +352,6 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
     const auto rs = make_rsrc(scale, uint32_t(n) * ng * 4u);
     const auto ra = make_rsrc(a16, uint32_t(n) * ng * 2u);
     const auto rb = make_rsrc(b16, uint32_t(n) * ng * 2u);
-    const auto rx = make_rsrc(x, uint32_t(m) * uint32_t(k) * 2u);
 
     // this lane's weight rows (block jb of the wave: row 16 jb + l % 16);
     // rows past the matrix repeat the last one, their outputs are not stored
@@ -388,10 +404,9 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
         }
     };
     auto load_x = [&](int st, uint8_t *buf) __attribute__((always_inline)) {
-        const uint32_t so = uint32_t(min(st, nsteps - 1)) * 128u;
+        const auto rx = step_rsrc(x, uint32_t(m) * uint32_t(k) * 2u, uint32_t(min(st, nsteps - 1)) * 128u);
 #pragma unroll
-        for (int t = 0; t < NX; ++t)
-            load_lds16(rx, buf + 1024 * (4 * t + wave), xoff[t], so);
+        for (int t = 0; t < NX; ++t) load_lds16(rx, buf + 1024 * (4 * t + wave), xoff[t]);
     };
 
     f32x4_t acc[BI][2];

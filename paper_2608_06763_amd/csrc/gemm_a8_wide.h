@@ -286,7 +286,6 @@ __global__ void __launch_bounds__(256, 2) gemm_a8_wide(
     const auto ra = make_rsrc(a16, uint32_t(n) * ng * 2u);
     const auto rb = make_rsrc(b16, uint32_t(n) * ng * 2u);
     const auto rt = make_rsrc(ctab, TB ? uint32_t(n) * ng * (1u << (B - 1)) : 0u);
-    const auto rx = make_rsrc(x8, uint32_t(m) * uint32_t(k));
 
     // this lane's weight rows (block jb of the wave: row 16 jb + l % 16); rows
     // past the matrix repeat the last one, their outputs are not stored
@@ -397,9 +396,9 @@ __global__ void __launch_bounds__(256, 2) gemm_a8_wide(
         }
     };
     auto load_x = [&](int st, uint8_t *buf) __attribute__((always_inline)) {
-        const uint32_t so = uint32_t(min(st, nsteps - 1)) * 128u;
+        const auto rx = step_rsrc(x8, uint32_t(m) * uint32_t(k), uint32_t(min(st, nsteps - 1)) * 128u);
 #pragma unroll
-        for (int t = 0; t < NX; ++t) load_lds16(rx, buf + 1024 * (4 * t + wave), xoff[t], so);
+        for (int t = 0; t < NX; ++t) load_lds16(rx, buf + 1024 * (4 * t + wave), xoff[t]);
     };
 
     float accf[BI][2][4];

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "cq_device.h"
+#include "stream_common.h"
 
 #include <type_traits>
 
@@ -17,10 +18,18 @@ __device__ __forceinline__ void unroll(F &&f) {
     }
 }
 
-// Every lane brings 16 bytes from its byte offset voff (+ soff) to LDS bytes
+// Every lane brings 16 bytes from its byte offset voff to LDS bytes
 // dst + 16 lane .. +15 (dst wave-uniform), without passing through registers.
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, uint8_t *dst, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, voff, soff, 0, 0);
+__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, uint8_t *dst, uint32_t voff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, voff, 0, 0, 0);
+}
+
+// Resource of the `bytes` at `base` from byte `off` on (wave-uniform): the range
+// check then covers a step's whole offset, and a last step that reads past the
+// tensor stays inside it.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t step_rsrc(const void *base, uint32_t bytes, uint32_t off) {
+    off = __builtin_amdgcn_readfirstlane(off);
+    return make_rsrc(static_cast<const uint8_t *>(base) + off, bytes - off);
 }
 
 // Keep loads in program order across this point, for the compiler (the kernel's

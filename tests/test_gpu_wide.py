@@ -91,6 +91,42 @@ def test_wide_model_dtype(torch_dev, bits, group, k, m, repeat):
             assert torch_dev.equal(y16, y.to(y16.dtype)), f
 
 
+def whole_bound(xv, wd):
+    """FP32 weights and products: the level within 2^-20, an FP32 sum over K."""
+    return (2.0 ** -20 + 2.0 ** -24 * np.sqrt(xv.shape[1]) * 4) * (np.abs(xv) @ np.abs(wd).T) + 1e-30
+
+
+# The split-K kernel: FP32-whole weights up to 16 rows (B >= 6, the generic
+# family), the many-row operands from 17 to 64 rows; K of 17 and 33 steps of 128
+# codes over eight waves (some with one step more, the last with none or a part),
+# ragged weight and activation rows.
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("group,k", [(32, 2176), (64, 2176), (128, 4224), (256, 2304), (512, 4608)])
+@pytest.mark.parametrize("m", [12, 16, 17, 33, 64])
+def test_split_model_dtype(torch_dev, bits, group, k, m):
+    import paper_2608_06763_amd as cq
+    if group == 32 and bits in (4, 8):
+        k = 2080  # a step with one unit
+    if (m <= 16 or m <= 32) and bits <= 5:
+        pytest.skip("the slab kernels' rows")
+    n = 75
+    w, codes, scale, a, b = random_weight(980 + bits, n, k, bits, group)
+    wd = F.decode(codes, bits, group, scale, a, b)
+    family = "gemv_generic" if m <= 16 else "gemm_mfma" if bits <= 5 else "gemm_tiled"
+    for dtype in ("bf16", "fp16"):
+        xb, xv = act(981 + m, m, k, dtype)
+        x = torch_dev.from_numpy(xb.view(np.int16)).cuda().view(
+            torch_dev.bfloat16 if dtype == "bf16" else torch_dev.float16)
+        say("split", bits, group, k, m, dtype, family)
+        y = cq.cq_gemm_model_dtype_family(w, x, family, y_dtype=torch_dev.float32)
+        assert torch_dev.equal(y, cq.cq_gemm_model_dtype_family(w, x, family, y_dtype=torch_dev.float32))
+        assert torch_dev.equal(y, cq.cq_gemm_model_dtype(w, x, y_dtype=torch_dev.float32))
+        bound = whole_bound(xv, wd) if m <= 16 else model_dtype_bound(xv, wd, dtype)
+        assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - xv @ wd.T) <= bound)
+        y16 = cq.cq_gemm_model_dtype(w, x)
+        assert torch_dev.equal(y16, y.to(y16.dtype))
+
+
 # A8: the wide kernel against the conservative one (whose partials dump keeps
 # it) bit for bit, both rescale the exact INT32 partials in group order, and
 # against the oracle's semantics.  Heights of 32 to 256 rows, K ending inside a
