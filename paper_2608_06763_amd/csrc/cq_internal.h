@@ -137,6 +137,10 @@ hipError_t launch_gemm_a8_mfma(const cq_weight &w, const int8_t *x8, const float
 bool gemm_a8_wide_supported(const cq_weight &w, int64_t m);
 hipError_t launch_gemm_a8_wide(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
                                void *y, int y_dt, int tile_rows, hipStream_t stream);
+// Few rows with split K (gemm_a8_split.h).
+bool gemm_a8_split_preferred(const cq_weight &w, int64_t m);
+hipError_t launch_gemm_a8_split(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y, int y_dt,
+                                hipStream_t stream);
 hipError_t launch_gemm_a8_tile(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
                                void *y, int y_dt, int tile_rows, hipStream_t stream);
 

@@ -471,8 +471,12 @@ bool gemm_a8_mfma_supported(const cq_weight &w, int64_t m) {
 }
 
 // x-tile height for m rows when the caller does not name one: up to 64 rows
-// the split-K tiles of gemm_a8_tile.hip, else the wide kernel (0: its choice)
-static int a8_mfma_tile_rows(int64_t m) { return m <= 32 ? 32 : m <= 64 ? 64 : 0; }
+// the tiles of gemm_a8_tile.hip (28672 x 8192 W4, 64 rows: 92 us, the wide
+// kernel 69 there), else the wide kernel (0: its choice)
+static int a8_mfma_tile_rows(const cq_weight &w, int64_t m) {
+    if (m > 64 || (m > 32 && w.n > 16384)) return 0;
+    return m <= 32 ? 32 : 64;
+}
 
 hipError_t launch_gemm_a8_mfma(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y, int y_dt,
                                int32_t *partials, int tile_rows, hipStream_t stream) {
@@ -482,14 +486,18 @@ hipError_t launch_gemm_a8_mfma(const cq_weight &w, const int8_t *x8, const float
         if (y_dt == 1) return a8_mfma_dump<1>(w, x8, dx, m, y, partials, stream);
         return a8_mfma_dump<2>(w, x8, dx, m, y, partials, stream);
     }
-    const int tr = tile_rows ? tile_rows : a8_mfma_tile_rows(m);
+    if (tile_rows == 0 && m > 32 && gemm_a8_split_preferred(w, m))
+        return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
+    const int tr = tile_rows ? tile_rows : a8_mfma_tile_rows(w, m);
     if (tr == 32 || tr == 64) return launch_gemm_a8_tile(w, nullptr, x8, dx, m, y, y_dt, tr, stream);
     return launch_gemm_a8_wide(w, nullptr, x8, dx, m, y, y_dt, tr, stream);
 }
 
 hipError_t launch_gemm_a8_mfma_tab(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx,
                                    int64_t m, void *y, int y_dt, hipStream_t stream) {
-    const int tr = a8_mfma_tile_rows(m);
+    // the split kernel's register decode forms the carriers of the table
+    if (m > 32 && gemm_a8_split_preferred(w, m)) return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
+    const int tr = a8_mfma_tile_rows(w, m);
     if (tr) return launch_gemm_a8_tile(w, ctab, x8, dx, m, y, y_dt, tr, stream);
     return launch_gemm_a8_wide(w, ctab, x8, dx, m, y, y_dt, 0, stream);
 }

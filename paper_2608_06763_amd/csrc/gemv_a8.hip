@@ -147,6 +147,8 @@ static hipError_t dispatch_bits(const cq_weight &w, const int8_t *x8, const floa
 
 hipError_t launch_gemv_a8_generic(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y, int y_dt,
                                   int32_t *partials, hipStream_t stream) {
+    // without a dump, two rows or more: the split-K kernel where it leads
+    if (!partials && gemm_a8_split_preferred(w, m)) return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
     if (y_dt == 0) return dispatch_bits<0>(w, x8, dx, m, y, partials, nullptr, stream);
     if (y_dt == 1) return dispatch_bits<1>(w, x8, dx, m, y, partials, nullptr, stream);
     return dispatch_bits<2>(w, x8, dx, m, y, partials, nullptr, stream);
@@ -154,10 +156,11 @@ hipError_t launch_gemv_a8_generic(const cq_weight &w, const int8_t *x8, const fl
 
 hipError_t launch_gemv_a8_tab(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
                               void *y, int y_dt, hipStream_t stream) {
-    // the single-row (B <= 4) and W4 narrow-row kernels form their carriers
-    // in registers (the same values); the generic kernel reads the table
+    // the single-row (B <= 4), W4 narrow-row and split-K kernels form their
+    // carriers in registers (the same values); the generic kernel reads the table
     if (gemv_a8_stream_supported(w, m)) return launch_gemv_a8_stream(w, x8, dx, y, y_dt, stream);
     if (gemv_a8_narrow_supported(w, m)) return launch_gemv_a8_narrow(w, x8, dx, m, y, y_dt, stream);
+    if (gemm_a8_split_preferred(w, m)) return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
     if (y_dt == 0) return dispatch_bits<0>(w, x8, dx, m, y, nullptr, ctab, stream);
     if (y_dt == 1) return dispatch_bits<1>(w, x8, dx, m, y, nullptr, ctab, stream);
     return dispatch_bits<2>(w, x8, dx, m, y, nullptr, ctab, stream);

@@ -133,7 +133,7 @@ def test_split_model_dtype(torch_dev, bits, group, k, m):
 # step for the smaller groups, G above and below a step.
 @pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("group,k", [(32, 1152), (64, 1152), (64, 1216), (128, 1152), (256, 1280), (512, 1536)])
-@pytest.mark.parametrize("m,repeat", [(17, 1), (130, 1), (500, 104)])
+@pytest.mark.parametrize("m,repeat", [(2, 1), (16, 1), (17, 1), (64, 1), (130, 1), (500, 104)])
 def test_wide_a8(torch_dev, bits, group, k, m, repeat):
     import paper_2608_06763_amd as cq
     from oracle import a8 as A8
@@ -150,17 +150,28 @@ def test_wide_a8(torch_dev, bits, group, k, m, repeat):
     x8, dx = torch_dev.from_numpy(x8_np).cuda(), torch_dev.from_numpy(dx_np.astype(np.float32)).cuda()
     families = ("gemm_tiled",)
     if bits in (3, 4) and group >= 64:
-        families = ("gemm_tiled", "gemm_mfma_m128", "gemm_mfma_m256") + (("gemm_mfma",) if m > 64 else ())
+        families = ("gemm_tiled", "gemm_mfma_m128", "gemm_mfma_m256") + (("gemm_mfma",) if m > 32 else ())
     base, _ = cq.cq_gemm_a8(w, x8, dx, y_dtype=torch_dev.float32, want_partials=True) if m * n * repeat < 1 << 20 \
         else (None, None)
     ref = None
     if repeat == 1:
         ref, _ = A8.gemm_a8(x8_np, dx_np, codes, bits, group, scale, a, b)
+    if m <= 16:
+        # W3 and W4 with G >= 64 have other kernels here
+        families = () if bits in (3, 4) and group >= 64 else ("gemv_generic",)
+        base = None
+    if m <= 64:
+        # the load-time tables hold the same carriers
+        tab = cq.cq_build_carriers(w)
+        say("wide a8 carriers", bits, group, k, m)
+        assert torch_dev.equal(cq.cq_gemm_a8_carriers(w, tab, x8, dx, y_dtype=torch_dev.float32),
+                               cq.cq_gemm_a8(w, x8, dx, y_dtype=torch_dev.float32))
     for f in families:
         say("wide a8", bits, group, k, m, repeat, f)
         y = cq.cq_gemm_a8_family(w, x8, dx, f, y_dtype=torch_dev.float32)
         assert torch_dev.equal(y, cq.cq_gemm_a8_family(w, x8, dx, f, y_dtype=torch_dev.float32)), f
-        if base is not None:
+        # (up to 64 rows the conservative family splits K, in another order)
+        if base is not None and (f not in ("gemm_tiled", "gemm_mfma") or m > 64):
             assert torch_dev.equal(y, base), f
         if repeat > 1:
             got = y.view(m, repeat, n)
@@ -184,11 +195,11 @@ def test_wide_a8_near_ties(torch_dev, bits, group):
         pytest.skip("rows must be whole 16-byte units")
     codes, s, a, b, x8, dx, p = carrier_probe(bits, group)
     w = cq.CQWeight.from_codes(codes, s, a, b, bits, group)
-    m = 70
-    x8_t = torch_dev.from_numpy(np.repeat(x8, m, axis=0)).cuda()
-    dx_t = torch_dev.from_numpy(np.repeat(dx, m)).cuda()
-    want = np.repeat(p.sum(axis=-1).astype(np.float64).reshape(1, -1), m, axis=0)
-    for f in ("gemm_tiled",) + (("gemm_mfma_m128",) if bits <= 4 and group >= 64 else ()):
-        say("wide near ties", bits, group, f)
-        y = cq.cq_gemm_a8_family(w, x8_t, dx_t, f, y_dtype=torch_dev.float32).cpu().numpy().astype(np.float64)
-        assert np.array_equal(y, want), f
+    for m in (20, 70):
+        x8_t = torch_dev.from_numpy(np.repeat(x8, m, axis=0)).cuda()
+        dx_t = torch_dev.from_numpy(np.repeat(dx, m)).cuda()
+        want = np.repeat(p.sum(axis=-1).astype(np.float64).reshape(1, -1), m, axis=0)
+        for f in ("gemm_tiled",) + (("gemm_mfma_m128",) if bits <= 4 and group >= 64 else ()):
+            say("wide near ties", bits, group, f, m)
+            y = cq.cq_gemm_a8_family(w, x8_t, dx_t, f, y_dtype=torch_dev.float32).cpu().numpy().astype(np.float64)
+            assert np.array_equal(y, want), f
