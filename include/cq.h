@@ -307,12 +307,15 @@ int64_t cq_get_gemv_max_rows(int32_t path);
  *   GEMV_NARROW   matrix-core narrow-row GEMV (model dtype 2 <= m <= 16,
  *                 B <= 5; A8 2 <= m <= 32, W3 and W4 with G >= 64, two
  *                 16-row blocks of x per decoded operand above 16 rows)
- *   GEMV_GENERIC  conservative one-wave-per-row GEMV (m <= 16, every B, G)
+ *   GEMV_GENERIC  conservative one-wave-per-row GEMV (m <= 16, every B, G);
+ *                 without a partials dump the split-K matrix-core kernels
+ *                 take the row counts on which they are faster
  *   GEMM_MFMA     tiled matrix-core GEMM (model dtype B <= 5; A8 W3/W4 with
  *                 G >= 64)
  *   GEMM_TILED    conservative tiled GEMM (every B, G): 64 x 64 tiles; A8
  *                 without a partials dump and model dtype B >= 6 run the wide
- *                 lane-decoded kernels where their 32-bit offsets reach
+ *                 lane-decoded kernels, or split K over few tiles, where
+ *                 their 32-bit offsets reach
  *   GEMM_MFMA_ROUNDED  model dtype only: the tiled matrix-core GEMM with the
  *                 decoded weight s_g q rounded once to the activation dtype
  *                 before the dot, the dense rounding point of Sec. 5.3 (BF16:
@@ -325,7 +328,8 @@ int64_t cq_get_gemv_max_rows(int32_t path);
  *   GEMM_MFMA_M32, _M64, _M128, _M256  GEMM_MFMA with a fixed x-tile height
  *                 (rows of x per workgroup tile; the tile-height dimension of
  *                 the selection in Sec. 5.6).  GEMM_MFMA picks 32 or 64 up to 64
- *                 rows and above that by the shape (an A8 partials dump
+ *                 rows and above that by the shape, or splits K where few
+ *                 tiles would leave compute units idle (an A8 partials dump
  *                 always runs the 256-row tile).  Same widths as GEMM_MFMA.
  *   GEMM_SLAB     model dtype only, 1 <= m <= 32, B <= 5: matrix-core GEMM for
  *                 few rows in which every lane decodes its codes straight into

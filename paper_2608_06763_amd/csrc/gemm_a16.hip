@@ -176,7 +176,7 @@ static hipError_t dispatch_bits(const cq_weight &w, const void *x, int64_t m, vo
 
 hipError_t launch_gemm_a16_tiled(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
                                  hipStream_t stream) {
-    // B >= 6, few rows: split K
+    // B >= 6, few tiles: split K
     if (w.bits >= 6 && gemm_a16_split_preferred(w, m))
         return launch_gemm_a16_split(w, x, x_dt, m, y, y_dt, false, stream);
     // B >= 6: the wide kernel (4096 x 14336 at 512 rows, W6 G128: 655 -> 126 us);

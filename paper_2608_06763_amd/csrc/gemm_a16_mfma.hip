@@ -13,8 +13,8 @@ bool gemm_a16_mfma_supported(const cq_weight &w, int64_t m) {
 // on the chip (W4 G128, K = 4096, 64 rows: 56 us at N = 4096 and 57 at 14336
 // against 63 and 64 for the 128-row tiles of gemm_a16_wide.h); above that the
 // wide kernel leads (128 rows: 63 and 66 us against 98).  The heights 128 and
-// 256 are the wide kernel's; every height accumulates in the same order.  33 to
-// 64 rows on few weight rows and long K take the split-K kernel.
+// 256 are the wide kernel's; every height accumulates in the same order.  More
+// than 32 rows whose tiles would leave compute units idle take the split-K kernel.
 hipError_t launch_gemm_a16_mfma(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
                                 int tile_rows, hipStream_t stream) {
     if (tile_rows == 0 && m > 32 && gemm_a16_split_preferred(w, m))

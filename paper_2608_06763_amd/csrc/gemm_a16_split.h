@@ -1,4 +1,4 @@
-// Model-dtype GEMM for few rows (1 <= m <= 64) with lane-decoded weight
+// Model-dtype GEMM for few rows or few output tiles with lane-decoded weight
 // operands and split K, every B and G, on gfx950 matrix cores.
 //
 // Tiling.  A workgroup owns 16 BI rows of x by 32 rows of W; its KS waves split
@@ -23,7 +23,8 @@
 // latency at two waves per SIMD.  Measured: 8192 x 8192 W8 G128, 8 rows 37 us
 // (80 for one wave per weight row); K in 64-code steps with 8 codes per lane and
 // unit 41; 16 waves 39.  4096 x 4096 W4, 48 rows 19 us (55 for 64-row tiles);
-// 14336 x 4096, 64 rows 46 (184).
+// 14336 x 4096, 64 rows 46 (184); 4096 x 4096 W4, 128 rows 38 (63 for the wide
+// kernel).
 #pragma once
 
 #include "gemm_a16_wide.h"

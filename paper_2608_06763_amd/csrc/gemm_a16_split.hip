@@ -47,14 +47,20 @@ bool gemm_a16_split_whole_preferred(const cq_weight &w, int64_t m) {
     return w.bits >= 6 && m <= 16 && gemm_a16_wide_supported(w, m) && (m >= 12 || (m >= 5 && w.n * w.k >= (1 << 24)));
 }
 
-// 17 to 64 rows.  Up to 32 rows one tile of x, against the wide kernel for B >=
-// 6 (W8, K = 4096, 17 rows: 73 / 23 us at N = 8192, 76 / 45 at 14336).  Two
-// tiles decode every weight twice, which pays while the other kernels leave
-// compute units idle (W4, K = 4096, 64 rows, 64-row tiles / split: 57 / 36 at N
-// = 8192, 57 / 68 at 14336; W8, wide / split: 73 / 45 and 76 / 87).  Each wave
-// should have two steps.
+// More than 16 rows.  Every tile of 32 x 32 decodes its weights anew, which pays
+// while the other kernels, whose tiles are larger, leave compute units idle: for
+// up to three rounds of tiles over the chip (other kernel / here, us; 64-row
+// tiles up to 64 rows of B <= 5, else the wide kernel).  One round: 8192 x 1024
+// W3 G64, 256 rows 151 / 31; 4096 x 2048 W8, 128 rows 73 / 25.  Two: 4096 x 4096
+// W4, 128 rows 63 / 38; 2048 x 8192, 64 rows 30 / 26, but W5 34 / 35 (3072 x
+// 8192: 50 / 42).  Three: 4096 x 4096, 192 rows W4 64 / 54, W8 75 / 69; 4096 x
+// 20000 W8, 20 rows 78 / 66; but 2048 x 4096 W3, 192 rows 35 / 39.  Four: 4096 x
+// 4096 W4, 256 rows 65 / 71.  Below K = 2048 a wave has fewer than two steps.
 bool gemm_a16_split_preferred(const cq_weight &w, int64_t m) {
-    return m <= 64 && w.k >= 2048 && gemm_a16_wide_supported(w, m) && (m <= 32 || w.n <= 8192);
+    if (!gemm_a16_wide_supported(w, m)) return false;
+    const int64_t rounds = split_rounds(w.n, m);
+    if (rounds > 3) return false;
+    return w.k >= (rounds == 3 ? 4096 : rounds == 2 && w.bits == 5 ? 3072 : 2048);
 }
 
 hipError_t launch_gemm_a16_split(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool whole,

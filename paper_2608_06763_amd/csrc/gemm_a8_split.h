@@ -1,4 +1,4 @@
-// Dynamic-A8 GEMM for few rows (1 <= m <= 64) with lane-decoded carriers and
+// Dynamic-A8 GEMM for few rows or few output tiles with lane-decoded carriers and
 // split K, every B and G, on gfx950 int8 matrix cores.
 //
 // Numerics and decoders are those of gemm_a8_wide.h: exact INT32 partials of
@@ -14,7 +14,7 @@
 // instructions a code) at one or two workgroups of eight waves per compute unit.
 // Measured with the quantizer: 8192 x 8192 W6 G64, 8 rows 38 us (96 for one wave
 // per weight row), 32 rows 42 (180); 3072 x 3584 W5 G512, 64 rows 20 (34 for the
-// wide kernel, 128 before it).
+// wide kernel, 128 before it); 8192 x 512 W5 G32, 128 rows 40 (370).
 #pragma once
 
 #include "gemm_a8_wide.h"

@@ -58,6 +58,12 @@ __device__ __forceinline__ int xcd_tile(int nwg) {
     return xcd * per + min(xcd, rem) + (int(blockIdx.x) >> 3);
 }
 
+// Rounds over the chip's 256 compute units that the 32 x 32 tiles of the split-K
+// kernels take.
+inline int64_t split_rounds(int64_t n, int64_t m) {
+    return ((m + 31) / 32 * ((n + 31) / 32) + 255) / 256;
+}
+
 // A use of the operand registers at this point: without one the compiler sinks
 // their computation below the matrix work it is meant to run beside.
 template <typename V>
