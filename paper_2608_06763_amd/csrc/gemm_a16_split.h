@@ -18,6 +18,14 @@
 // is split exactly into two BF16 numbers; otherwise the weight is one FP16
 // operand, as in the many-row kernels.
 //
+// A matrix instruction cuts its sum off below (its result is low by about a
+// tenth of a unit of 2^-24, measured), so a chain of them drifts: with one chain
+// over all of K the relative error of FP32 outputs was 3.6e-7 at K = 8192 and
+// 5.1e-7 at 16384 (W8, BF16).  With three parts only the products of the same 32 codes
+// meet in one chain, the smallest first; the chains' sums are added in FP32, by
+// pairs within a step, and every other step has its weights negated: 1.0e-7 and
+// 1.2e-7, the FP32 GEMV 1.4e-7 at both.
+//
 // What bounds it: VALU issue of the decode (W8 in three parts about 12
 // instructions a code: 8192 x 8192 needs 20 us of it on every SIMD) and its
 // latency at two waves per SIMD.  Measured: 8192 x 8192 W8 G128, 8 rows 37 us
@@ -215,9 +223,11 @@ __global__ void __launch_bounds__(64 * KS) gemm_a16_split(
         const uint8_t *buf = xbuf(p_c);
         const wslot &o = ws[P];
         const bool in = 4 * st + q < units;
+        const float sg = PARTS == 3 && (st & 1) ? -1.f : 1.f;
         decoder_t<B, WDT> d[2];
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) d[jb].template build<G128>(in ? o.s[jb] : 0.f, o.a[jb], o.b[jb], q);
+        for (int jb = 0; jb < 2; ++jb) d[jb].template build<G128>(in ? sg * o.s[jb] : 0.f, o.a[jb], o.b[jb], q);
+        f32x4_t sum[2], half[2];  // PARTS == 3: chains' sums of this step
         unroll<0, 4>([&](auto c_c) __attribute__((always_inline)) {
             constexpr int C = decltype(c_c)::value;
             uint32_t op[2][PARTS][4];
@@ -228,21 +238,36 @@ __global__ void __launch_bounds__(64 * KS) gemm_a16_split(
                 u32x4 xf = *reinterpret_cast<const u32x4 *>(buf + 16 * i * kSRow + xrow +
                                                             16u * uint32_t((4 * q + C) ^ (lane & 7)));
                 if (!in) xf = u32x4{0, 0, 0, 0};
-                auto mul = [&](const u32x4 &xv) __attribute__((always_inline)) {
-#pragma unroll
-                    for (int p = 0; p < PARTS; ++p)
-#pragma unroll
-                        for (int jb = 0; jb < 2; ++jb)
-                            acc[i][jb] = mma<WDT>(u32x4{op[jb][p][0], op[jb][p][1], op[jb][p][2], op[jb][p][3]}, xv,
-                                                  acc[i][jb]);
+                auto mul = [&](auto p_c, int jb, const u32x4 &xv, f32x4_t c) __attribute__((always_inline)) {
+                    constexpr int Q = decltype(p_c)::value;
+                    return mma<WDT>(u32x4{op[jb][Q][0], op[jb][Q][1], op[jb][Q][2], op[jb][Q][3]}, xv, c);
                 };
-                if constexpr (XDT == 1 && PARTS == 3) {
-                    u32x4 h, l;
-                    split_x(xf, h, l);
-                    mul(h);
-                    mul(l);
+                if constexpr (PARTS == 3) {
+                    u32x4 h = xf, l;
+                    if constexpr (XDT == 1) split_x(xf, h, l);
+                    // the smallest products first
+                    f32x4_t p[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+                    unroll<0, 3>([&](auto r_c) __attribute__((always_inline)) {
+                        using Q = std::integral_constant<int, 2 - decltype(r_c)::value>;
+                        if constexpr (XDT == 1) {
+#pragma unroll
+                            for (int jb = 0; jb < 2; ++jb) p[jb] = mul(Q{}, jb, l, p[jb]);
+                        }
+#pragma unroll
+                        for (int jb = 0; jb < 2; ++jb) p[jb] = mul(Q{}, jb, h, p[jb]);
+                    });
+#pragma unroll
+                    for (int jb = 0; jb < 2; ++jb) {
+                        if constexpr (C == 0) sum[jb] = p[jb];
+                        else if constexpr (C == 1) sum[jb] += p[jb];
+                        else if constexpr (C == 2) half[jb] = p[jb];
+                        else acc[i][jb] += sg * (sum[jb] + (half[jb] + p[jb]));
+                    }
                 } else {
-                    mul(xf);
+                    unroll<0, PARTS>([&](auto p_c) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int jb = 0; jb < 2; ++jb) acc[i][jb] = mul(p_c, jb, xf, acc[i][jb]);
+                    });
                 }
             }
         });

@@ -144,12 +144,24 @@ struct curve_decoder {
             b = bv;
             c = cv;
         } else {
-            // s and the powers of 1/M folded into the coefficients
-            constexpr float M = float(max_code(B));
-            a = sv * av * (1.f / M);
-            b = sv * bv * (1.f / (M * M));
-            c = sv * cv * (1.f / (M * M * M));
+            // s and the powers of 1/M folded into the coefficients, each rounded
+            // once: a formed weight is within 0.7 units of 2^-24 (rms), 0.8 for a
+            // correctly rounded k/M in the Horner form and 1.0 to 1.2 with a
+            // rounding for every factor
+            constexpr int M = max_code(B);
+            a = folded<M>(sv, av);
+            b = folded<M * M>(sv, bv);
+            c = folded<M * M * M>(sv, cv);
         }
+    }
+    // s v / D with one rounding (up to a remainder of 2^-46): the quotient's
+    // remainder is exact, D having at most 21 bits
+    template <int D>
+    static __device__ __forceinline__ float folded(float sv, float v) {
+        constexpr float rd = 1.f / float(D);
+        const float h = v * rd;
+        const float l = __builtin_fmaf(-h, float(D), v) * rd;
+        return __builtin_fmaf(sv, h, sv * l);
     }
     __device__ __forceinline__ float level(int k) const {
         const float kf = float(k);

@@ -92,8 +92,34 @@ def test_wide_model_dtype(torch_dev, bits, group, k, m, repeat):
 
 
 def whole_bound(xv, wd):
-    """FP32 weights and products: the level within 2^-20, an FP32 sum over K."""
-    return (2.0 ** -20 + 2.0 ** -24 * np.sqrt(xv.shape[1]) * 4) * (np.abs(xv) @ np.abs(wd).T) + 1e-30
+    """FP32 weights and products: coefficients rounded once and three Horner
+    roundings, up to twice that where the curve's terms cancel (8 units of
+    2^-24), and an FP32 sum over K."""
+    return (2.0 ** -21 + 2.0 ** -24 * np.sqrt(xv.shape[1]) * 4) * (np.abs(xv) @ np.abs(wd).T) + 1e-30
+
+
+# Up to 16 rows the split-K kernel stands in for the FP32 GEMV, which still runs
+# calls of four rows: its FP32 outputs are no further from the 64-bit result
+# (norm over 16 x 64 outputs; one chain of matrix instructions over all of K was
+# 2.6 times further at this K).
+@pytest.mark.parametrize("bits", [6, 7, 8])
+@pytest.mark.parametrize("group", [32, 128, 512])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_split_whole_precision(torch_dev, bits, group, dtype):
+    import paper_2608_06763_amd as cq
+    k, n, repeat, m = 8192, 64, 128, 16
+    w, codes, scale, a, b = random_weight(970 + bits, n, k, bits, group, repeat)
+    xb, xv = act(971 + group, m, k, dtype)
+    x = torch_dev.from_numpy(xb.view(np.int16)).cuda().view(
+        torch_dev.bfloat16 if dtype == "bf16" else torch_dev.float16)
+    want = xv @ F.decode(codes, bits, group, scale, a, b).T
+    say("split whole precision", bits, group, dtype)
+    y = cq.cq_gemm_model_dtype(w, x, y_dtype=torch_dev.float32)[:, :n]
+    base = torch_dev.cat([cq.cq_gemm_model_dtype_family(w, x[i:i + 4].contiguous(), "gemv_generic",
+                                                        y_dtype=torch_dev.float32)[:, :n] for i in range(0, m, 4)])
+    err, err_base = (np.linalg.norm(v.cpu().numpy().astype(np.float64) - want) for v in (y, base))
+    assert not torch_dev.equal(y, base)  # the split kernel ran
+    assert err <= err_base, (err, err_base)
 
 
 # The split-K kernel: FP32-whole weights up to 16 rows (B >= 6, the generic
