@@ -125,6 +125,10 @@ cq_status cq_decode_ref(const cq_weight *w, int8_t *codes_out, float *w_out, voi
  *   x        device [M, K] in x_dtype (CQ_BF16 or CQ_FP16), row-major.
  *   m        rows of x, >= 1.
  *   y        device [M, N] in y_dtype: x_dtype, or CQ_FP32 (diagnostics).
+ * Activations are meant to be finite.  An infinity or a NaN leaves no finite
+ * value in its row and does not reach other rows; whether an output of the row
+ * is an infinity or a NaN depends on the kernel where the operand is carried in
+ * two parts (B <= 5 from two rows, B >= 6 above 16 rows).
  * The result is deterministic for a given device, shape and dtype.
  */
 cq_status cq_gemm_model_dtype(const cq_weight *w, const void *x, cq_dtype x_dtype, int64_t m,

@@ -16,7 +16,8 @@
 // up to 16 rows, where the products are FP32 otherwise too; two are hi + lo as
 // in the many-row kernels.  FP16 activations: with three parts every activation
 // is split exactly into two BF16 numbers; otherwise the weight is one FP16
-// operand, as in the many-row kernels.
+// operand, as in the many-row kernels.  Infinite activations give what FP32
+// products give, with three parts: their sign times the weight's, NaN for 0.
 //
 // A matrix instruction cuts its sum off below (its result is low by about a
 // tenth of a unit of 2^-24, measured), so a chain of them drifts: with one chain
@@ -118,12 +119,24 @@ __device__ __forceinline__ void split_x(const u32x4 &xf, u32x4 &hi, u32x4 &lo) {
     }
 }
 
+// BF16 pairs with infinities and NaNs replaced by 0
+__device__ __forceinline__ u32x4 finite_only(const u32x4 &h, const u32x4 &v) {
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        // an exponent of all ones in h carries into the half's top bit
+        const uint32_t bad = (((h[e] & 0x7f807f80u) + 0x00800080u) >> 15) & 0x00010001u;
+        o[e] = v[e] & ~(bad * 0xffffu);
+    }
+    return o;
+}
+
 }  // namespace a16_split
 
 // G128: G >= 128, so that the four lanes of a row share a group and form W4's
 // tables together.
 template <int B, bool G128, int XDT, int BI, int PARTS, int KS>
-__global__ void __launch_bounds__(64 * KS) gemm_a16_split(
+__global__ void __launch_bounds__(64 * KS, PARTS == 3 ? 4 : 1) gemm_a16_split(
     const uint8_t *codes, const float *scale, const uint16_t *a16, const uint16_t *b16, int units_per_group, int n,
     int k, const uint16_t *x, int m, void *y, int y_dt, int tiles_m, int tiles_n) {
     using namespace a16_split;
@@ -214,6 +227,7 @@ __global__ void __launch_bounds__(64 * KS) gemm_a16_split(
     // Step st reads buffer and slot P = (st - s0) % NB.  Its activations were
     // requested NB - 1 steps ago; the wait counts the loads issued since.
     constexpr int kAfter = (NB - 1) * kW + (NB - 2) * NX;
+    bool inf = false;  // PARTS == 3: the second pass below
     auto do_step = [&](int st, auto p_c) __attribute__((always_inline)) {
         constexpr int P = decltype(p_c)::value;
         wait_loads<(kAfter < 62 ? kAfter : 62)>();
@@ -243,19 +257,25 @@ __global__ void __launch_bounds__(64 * KS) gemm_a16_split(
                     return mma<WDT>(u32x4{op[jb][Q][0], op[jb][Q][1], op[jb][Q][2], op[jb][Q][3]}, xv, c);
                 };
                 if constexpr (PARTS == 3) {
-                    u32x4 h = xf, l;
+                    u32x4 h = xf, l = xf;
                     if constexpr (XDT == 1) split_x(xf, h, l);
                     // the smallest products first
                     f32x4_t p[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
-                    unroll<0, 3>([&](auto r_c) __attribute__((always_inline)) {
-                        using Q = std::integral_constant<int, 2 - decltype(r_c)::value>;
-                        if constexpr (XDT == 1) {
+                    auto chain = [&](const u32x4 &hf, const u32x4 &lf) __attribute__((always_inline)) {
+                        unroll<0, 3>([&](auto r_c) __attribute__((always_inline)) {
+                            using Q = std::integral_constant<int, 2 - decltype(r_c)::value>;
+                            if constexpr (XDT == 1) {
 #pragma unroll
-                            for (int jb = 0; jb < 2; ++jb) p[jb] = mul(Q{}, jb, l, p[jb]);
-                        }
+                                for (int jb = 0; jb < 2; ++jb) p[jb] = mul(Q{}, jb, lf, p[jb]);
+                            }
 #pragma unroll
-                        for (int jb = 0; jb < 2; ++jb) p[jb] = mul(Q{}, jb, h, p[jb]);
-                    });
+                            for (int jb = 0; jb < 2; ++jb) p[jb] = mul(Q{}, jb, Q::value == 0 ? h : hf, p[jb]);
+                        });
+                    };
+                    // activations that are not finite meet the first weight part
+                    // only, which is 0 where the weight is
+                    if (__builtin_expect(inf, 0)) chain(finite_only(h, h), XDT == 1 ? finite_only(h, l) : l);
+                    else chain(h, l);
 #pragma unroll
                     for (int jb = 0; jb < 2; ++jb) {
                         if constexpr (C == 0) sum[jb] = p[jb];
@@ -275,16 +295,37 @@ __global__ void __launch_bounds__(64 * KS) gemm_a16_split(
         load_w(st + NB, ws[P]);
         vmem_order();
     };
-    if (s0 < s1) {
-        unroll<0, NB>([&](auto p_c) __attribute__((always_inline)) { load_w(s0 + decltype(p_c)::value, ws[decltype(p_c)::value]); });
-        unroll<0, NB - 1>([&](auto p_c) __attribute__((always_inline)) { load_x(s0 + decltype(p_c)::value, xbuf(p_c)); });
+    while (s0 < s1) {
+        // (opaque, so that no address of this rare loop's start is kept in a register)
+        int first = s0;
+        if constexpr (PARTS == 3) __asm__ volatile("" : "+s"(first));
+        unroll<0, NB>([&](auto p_c) __attribute__((always_inline)) { load_w(first + decltype(p_c)::value, ws[decltype(p_c)::value]); });
+        unroll<0, NB - 1>([&](auto p_c) __attribute__((always_inline)) { load_x(first + decltype(p_c)::value, xbuf(p_c)); });
         wait_loads<0>();
-        for (int st = s0;;) {
+        for (int st = first;;) {
             do_step(st, std::integral_constant<int, 0>{});
             if (++st == s1) break;
             do_step(st, std::integral_constant<int, 1>{});
             if (++st == s1) break;
         }
+        if (PARTS != 3 || inf) break;
+        // An activation that is not finite leaves no finite sum in its row and
+        // may have met a weight part of 0, or of another sign: only then this
+        // wave goes over its steps again.
+        float bad = 0.f;
+#pragma unroll
+        for (int i = 0; i < BI; ++i)
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bad += acc[i][jb][e] - acc[i][jb][e];
+        if (__builtin_expect(!__any(!(bad == 0.f)), 1)) break;
+        inf = true;
+#pragma unroll
+        for (int i = 0; i < BI; ++i)
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb) acc[i][jb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        wait_loads<0>();
     }
     wait_loads<0>();
     __syncthreads();

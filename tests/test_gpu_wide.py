@@ -153,6 +153,46 @@ def test_split_model_dtype(torch_dev, bits, group, k, m):
         assert torch_dev.equal(y16, y.to(y16.dtype))
 
 
+# Infinities and NaNs of one activation row, on both sides of the row count from
+# which the split-K kernel takes W6-W8: what FP32 products give (a zero weight
+# against an infinity is NaN), and the other rows as without them.
+@pytest.mark.parametrize("bits", [6, 7, 8])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("group", [32, 128])
+def test_few_rows_nonfinite(torch_dev, bits, dtype, group):
+    import paper_2608_06763_amd as cq
+    k, n, repeat, m = 4224, 64, 64, 16
+    w, codes, scale, a, b = random_weight(975 + bits, n, k, bits, group, repeat)
+    wd = F.decode(codes, bits, group, scale, a, b)
+    xb, xv = act(976, m, k, dtype)
+    x = torch_dev.from_numpy(xb.view(np.int16)).cuda().view(
+        torch_dev.bfloat16 if dtype == "bf16" else torch_dev.float16)
+    bad, inf = x.clone(), float("inf")
+    # single infinities at the ends of K and inside, two in one row, a NaN
+    marks = {1: {0: inf}, 2: {k - 1: -inf}, 6: {2000: inf}, 9: {5: inf, 4000: inf}, 11: {77: inf, 78: -inf},
+             15: {3000: float("nan")}}
+    for r, at in marks.items():
+        for j, v in at.items():
+            bad[r, j] = v
+            xv[r, j] = v
+    rows = sorted(marks)
+    with np.errstate(invalid="ignore"):
+        want = (xv[rows][:, None, :] * wd[None]).sum(-1)
+    for rows_per_call in (16, 4):
+        say("nonfinite", bits, dtype, group, rows_per_call)
+        run = lambda v: torch_dev.cat([cq.cq_gemm_model_dtype_family(w, v[i:i + rows_per_call].contiguous(),
+                                       "gemv_generic", y_dtype=torch_dev.float32)[:, :n]
+                                       for i in range(0, m, rows_per_call)])
+        clean, y = run(x), run(bad)
+        if rows_per_call == 16:
+            assert torch_dev.allclose(y, cq.cq_gemm_model_dtype(w, bad, y_dtype=torch_dev.float32)[:, :n], rtol=0,
+                                      atol=0, equal_nan=True)
+        others = [r for r in range(m) if r not in marks]
+        assert torch_dev.equal(y[others], clean[others])
+        got = y[rows].cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, want, equal_nan=True)
+
+
 # A8: the wide kernel against the conservative one (whose partials dump keeps
 # it) bit for bit, both rescale the exact INT32 partials in group order, and
 # against the oracle's semantics.  Heights of 32 to 256 rows, K ending inside a
