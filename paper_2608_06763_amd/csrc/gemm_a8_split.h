@@ -104,6 +104,15 @@ __global__ void __launch_bounds__(64 * KS) gemm_a8_split(
         for (int t = 0; t < NX; ++t) load_lds16(rx, buf + 1024 * t, xoff[t]);
     };
 
+    // row factors of the outputs, requested here so that no store waits for one
+    const auto rd = make_rsrc(dx, uint32_t(m) * 4u);
+    float f[BI][4];
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f[i][r] = load_f32(rd, uint32_t(m0 + 16 * i + 4 * q + r) * 4u);
+    vmem_order();
+
     const i32x4 zero = {0, 0, 0, 0};
     f32x4 accf[BI][2];
     i32x4 part[GM == 0 ? BI : 1][2];  // INT32 partials of groups longer than a step
@@ -283,13 +292,13 @@ __global__ void __launch_bounds__(64 * KS) gemm_a8_split(
         for (int r = 0; r < 4; ++r) {
             const int row = m0 + 16 * i + 4 * q + r;
             if (row >= m) continue;
-            const float f = dx[row] / 127.0f;
+            const float fr = f[i][r] / 127.0f;
 #pragma unroll
             for (int jb = 0; jb < 2; ++jb) {
                 const int col = n0 + 16 * jb + (lane & 15);
                 if (col >= n) continue;
                 const int64_t at = int64_t(row) * n + col;
-                const float v = accf[i][jb][r] * f;
+                const float v = accf[i][jb][r] * fr;
                 if (y_dt == 0) store_out<0>(y, at, v);
                 else if (y_dt == 1) store_out<1>(y, at, v);
                 else store_out<2>(y, at, v);
