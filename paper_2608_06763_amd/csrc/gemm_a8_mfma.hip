@@ -1,6 +1,6 @@
-// Dynamic-A8 many-row GEMM (Sec. 5.4) for W4 with the INT32 partials dump, on
-// gfx950 int8 matrix cores, and the choice among the many-row kernels (without
-// a dump: gemm_a8_tile.hip up to 64 rows, else gemm_a8_wide.h).
+// Dynamic-A8 many-row GEMM (Sec. 5.4) for W3 and W4 on gfx950 int8 matrix cores,
+// W4 also with the INT32 partials dump, and the choice among the many-row
+// kernels of these widths (gemm_a8_tile.hip, gemm_a8_wide.h, gemm_a8_split.h).
 //
 // Numerics are eq. a8-output: INT8 activations times exact INT8 weight
 // carriers (eq. carrier) accumulate into exact INT32 group partials P_g
@@ -432,7 +432,11 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_a8_mfma(
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int col = n0 + wn + 16 * j + (lane & 15);
-                if (col < n) store_out<YDT>(y, int64_t(row) * n + col, accf[i][j][e] * f);
+                float v = accf[i][j][e] * f;
+                // (rounded to FP32 first, as in the wide kernel: the compiler
+                // would fuse product and FP16 conversion)
+                if constexpr (YDT == 1 && !DUMP) __asm__ volatile("" : "+v"(v));
+                if (col < n) store_out<YDT>(y, int64_t(row) * n + col, v);
             }
         }
 }
@@ -450,16 +454,29 @@ static hipError_t a8_mfma_launch(const cq_weight &w, const int8_t *x8, const flo
     return hipGetLastError();
 }
 
-// The partials dump runs four waves per workgroup, which leaves room for its
-// extra registers.
-template <int YDT>
-static hipError_t a8_mfma_dump(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y,
-                               int32_t *partials, hipStream_t stream) {
+template <int B, int YDT, bool TB>
+static hipError_t a8_mfma_group(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y,
+                                int32_t *partials, const int8_t *ctab, hipStream_t stream) {
+    // The partials dump (a test path) runs four waves per workgroup, which
+    // leaves room for its extra registers; the fast path runs eight.
+    if (partials) {
+        if constexpr (B != 4) {
+            return hipErrorNotSupported;  // W3 partials: the 64x64 kernel
+        } else {
+        switch (w.group) {
+            case 64: return a8_mfma_launch<B, 2, 2, 2, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
+            case 128: return a8_mfma_launch<B, 2, 2, 4, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
+            case 256: return a8_mfma_launch<B, 2, 2, 8, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
+            case 512: return a8_mfma_launch<B, 2, 2, 16, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
+        }
+        return hipErrorNotSupported;
+        }
+    }
     switch (w.group) {
-        case 64: return a8_mfma_launch<4, 2, 2, 2, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
-        case 128: return a8_mfma_launch<4, 2, 2, 4, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
-        case 256: return a8_mfma_launch<4, 2, 2, 8, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
-        case 512: return a8_mfma_launch<4, 2, 2, 16, YDT, true, false>(w, x8, dx, m, y, partials, nullptr, stream);
+        case 64: return a8_mfma_launch<B, 4, 2, 2, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
+        case 128: return a8_mfma_launch<B, 4, 2, 4, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
+        case 256: return a8_mfma_launch<B, 4, 2, 8, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
+        case 512: return a8_mfma_launch<B, 4, 2, 16, YDT, false, TB>(w, x8, dx, m, y, partials, ctab, stream);
     }
     return hipErrorNotSupported;
 }
@@ -470,36 +487,75 @@ bool gemm_a8_mfma_supported(const cq_weight &w, int64_t m) {
            stream_fits(w.n, w.k, w.bits, w.group) && w.n < lim && m < lim;
 }
 
-// x-tile height for m rows when the caller does not name one: up to 64 rows
-// the tiles of gemm_a8_tile.hip (28672 x 8192 W4, 64 rows: 92 us, the wide
-// kernel 69 there), else the wide kernel (0: its choice)
+template <bool TB>
+static hipError_t a8_mfma_dispatch(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx,
+                                   int64_t m, void *y, int y_dt, int32_t *partials, hipStream_t stream) {
+    if (w.bits == 3) {
+        if (y_dt == 0) return a8_mfma_group<3, 0, TB>(w, x8, dx, m, y, partials, ctab, stream);
+        if (y_dt == 1) return a8_mfma_group<3, 1, TB>(w, x8, dx, m, y, partials, ctab, stream);
+        return a8_mfma_group<3, 2, TB>(w, x8, dx, m, y, partials, ctab, stream);
+    }
+    if (y_dt == 0) return a8_mfma_group<4, 0, TB>(w, x8, dx, m, y, partials, ctab, stream);
+    if (y_dt == 1) return a8_mfma_group<4, 1, TB>(w, x8, dx, m, y, partials, ctab, stream);
+    return a8_mfma_group<4, 2, TB>(w, x8, dx, m, y, partials, ctab, stream);
+}
+
+// x-tile height for m rows when the caller does not name one, 0 for the wide
+// kernel (at its own choice).  Up to 64 rows the tiles of gemm_a8_tile.hip
+// (28672 x 8192 W4, 64 rows: 92 us, the wide kernel 69 there).  Above, the wide
+// kernel and the tiles of 128 (up to 128 rows) and 256 rows, whose eight waves
+// hide more of their latency where there is one workgroup to a compute unit and
+// which decode a weight once for twice the rows at G != 128.  `over(h)`: the wide
+// kernel's tiles of h rows need more than one round over the chip.  Measured, us,
+// wide / these, W4:
+//   G = 64, one round of 64 rows (32 up to 128 rows): 3072 x 8192, 200 rows
+//     63 / 78, 100 rows 55 / 58; more: 3072 x 5000, 1200 rows 135 / 86,
+//     14336 x 28672, 100 rows 346 / 259, 1024 x 28672, 2500 rows 418 / 277
+//   G = 128, one round of 256 rows here: 1024 x 8192, 700 rows 44 / 30, 3072 x
+//     13000, 400 rows 70 / 59, 8192 x 13000, 400 rows 139 / 137; up to three:
+//     1024 x 28672, 700 rows 85 / 76, 3072 x 8192, 1200 rows 100 / 112; four:
+//     1024 x 28672, 1000 rows 102 / 103
+//   G >= 256, two wide rounds for one here: 1024 x 5000, 1200 rows 31 / 26, 3072 x
+//     28672, 256 rows 52 / 48, 8192 x 5000, 1200 rows 107 / 103, 14336 x 5000 164 /
+//     165; three for two: 3072 x 8192, 1200 rows 75 / 88, 1024 x 8192 45 / 45
 static int a8_mfma_tile_rows(const cq_weight &w, int64_t m) {
-    if (m > 64 || (m > 32 && w.n > 16384)) return 0;
-    return m <= 32 ? 32 : 64;
+    if (m <= 32) return 32;
+    if (m <= 64) return w.n > 16384 ? 0 : 64;
+    const int64_t tn = (w.n + 127) / 128;
+    auto rounds = [&](int64_t h) { return ((m + h - 1) / h * tn + 255) / 256; };
+    auto over = [&](int64_t h) { return rounds(h) > 1; };
+    const int rows = m <= 128 ? 128 : 256;
+    bool here;
+    if (w.group == 64) here = over(m <= 128 ? 32 : 64);
+    else if (m <= 128) here = w.k < 2048 && over(64);
+    else if (!over(128)) here = false;
+    else if (w.group == 128) here = w.k < 2048 ? rounds(256) <= 3 : w.k < 8192 && !over(256);
+    else here = w.k < 2048 || (w.k <= 8192 && rounds(128) == 2 * rounds(256));
+    return here ? rows : 0;
+}
+
+static hipError_t a8_mfma_rows(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
+                               void *y, int y_dt, int tile_rows, hipStream_t stream) {
+    // (split K: its register decode forms the carriers of the table)
+    if (tile_rows == 0 && m > 32 && gemm_a8_split_preferred(w, m))
+        return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
+    const int tr = tile_rows ? tile_rows : a8_mfma_tile_rows(w, m);
+    if (tr == 0) return launch_gemm_a8_wide(w, ctab, x8, dx, m, y, y_dt, 0, stream);
+    if (tr < 256) return launch_gemm_a8_tile(w, ctab, x8, dx, m, y, y_dt, tr, stream);
+    if (ctab) return a8_mfma_dispatch<true>(w, ctab, x8, dx, m, y, y_dt, nullptr, stream);
+    return a8_mfma_dispatch<false>(w, nullptr, x8, dx, m, y, y_dt, nullptr, stream);
 }
 
 hipError_t launch_gemm_a8_mfma(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y, int y_dt,
                                int32_t *partials, int tile_rows, hipStream_t stream) {
-    if (partials) {
-        if (w.bits != 4) return hipErrorNotSupported;  // W3 partials: the 64 x 64 kernel
-        if (y_dt == 0) return a8_mfma_dump<0>(w, x8, dx, m, y, partials, stream);
-        if (y_dt == 1) return a8_mfma_dump<1>(w, x8, dx, m, y, partials, stream);
-        return a8_mfma_dump<2>(w, x8, dx, m, y, partials, stream);
-    }
-    if (tile_rows == 0 && m > 32 && gemm_a8_split_preferred(w, m))
-        return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
-    const int tr = tile_rows ? tile_rows : a8_mfma_tile_rows(w, m);
-    if (tr == 32 || tr == 64) return launch_gemm_a8_tile(w, nullptr, x8, dx, m, y, y_dt, tr, stream);
-    return launch_gemm_a8_wide(w, nullptr, x8, dx, m, y, y_dt, tr, stream);
+    // the partials dump is written by the 256-row kernel's four-wave variant
+    if (partials) return a8_mfma_dispatch<false>(w, nullptr, x8, dx, m, y, y_dt, partials, stream);
+    return a8_mfma_rows(w, nullptr, x8, dx, m, y, y_dt, tile_rows, stream);
 }
 
 hipError_t launch_gemm_a8_mfma_tab(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx,
                                    int64_t m, void *y, int y_dt, hipStream_t stream) {
-    // the split kernel's register decode forms the carriers of the table
-    if (m > 32 && gemm_a8_split_preferred(w, m)) return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
-    const int tr = a8_mfma_tile_rows(w, m);
-    if (tr) return launch_gemm_a8_tile(w, ctab, x8, dx, m, y, y_dt, tr, stream);
-    return launch_gemm_a8_wide(w, ctab, x8, dx, m, y, y_dt, 0, stream);
+    return a8_mfma_rows(w, ctab, x8, dx, m, y, y_dt, 0, stream);
 }
 
 }  // namespace cq

@@ -1,4 +1,4 @@
-// Dynamic-A8 tiled GEMM for moderate row counts (m <= 64) on gfx950 int8
+// Dynamic-A8 tiled GEMM for moderate row counts (m <= 128) on gfx950 int8
 // matrix cores, W3 and W4 (Sec. 5.4; the regime between the single-row GEMV
 // and the many-row GEMM of Sec. 5.5).
 //
@@ -7,9 +7,9 @@
 // group partials (eq. a8-int32-bound), each rescaled by s_g in FP32 at the
 // group's last step; the row factor d_x / 127 multiplies the sum.
 //
-// Tiling.  A workgroup owns a TM x TN tile of y (TM = 32 or 64 rows of x,
-// so no matrix work is spent on absent rows, and TN = 64 rows of W, which puts
-// hundreds of workgroups on the chip even for a single x tile).
+// Tiling.  A workgroup owns a TM x TN tile of y (TM = 32, 64 or 128 rows of
+// x, so no matrix work is spent on absent rows, and TN = 64 or 128 rows of W,
+// which puts hundreds of workgroups on the chip even for a single x tile).
 // Its waves each own a (16 BI) x (16 BJ) block and issue
 // v_mfma_i32_16x16x64_i8.  K advances 64 codes per step through two LDS
 // buffers with one barrier per step: every thread decodes its 16 codes of
@@ -62,6 +62,7 @@ struct a8_tile {
 };
 using a8_tile32 = a8_tile<1, 4, 2, 1, 8, 4>;    // 32 x 64, four waves of 32 x 16, up to four K-groups
 using a8_tile64 = a8_tile<1, 4, 4, 1, 8, 2>;    // 64 x 64, four waves of 64 x 16, up to two K-groups
+using a8_tile128 = a8_tile<2, 4, 4, 2, 8, 1>;   // 128 x 128, eight waves of 64 x 32
 
 template <int P0, int PN, typename F>
 __device__ __forceinline__ void unroll_slots(F &&f) {
@@ -345,7 +346,12 @@ __global__ void __launch_bounds__(T::NT * T::KSM) gemm_a8_tile(
 #pragma unroll
             for (int j = 0; j < BJ; ++j) {
                 const int col = n0 + wn + 16 * j + (lane & 15);
-                if (col < n) store_out<YDT>(y, int64_t(row) * n + col, accf[i][j][e] * f);
+                float v = accf[i][j][e] * f;
+                // (128 rows: rounded to FP32 first, as in the wide kernel, which
+                // serves other shapes of these row counts; the compiler would
+                // fuse product and FP16 conversion)
+                if constexpr (YDT == 1 && TM == 128) __asm__ volatile("" : "+v"(v));
+                if (col < n) store_out<YDT>(y, int64_t(row) * n + col, v);
             }
         }
 }
@@ -421,6 +427,7 @@ hipError_t a8_tile_rows(const cq_weight &w, const int8_t *ctab, const int8_t *x8
     switch (tile_rows) {
         case 32: return a8_tile_dtypes<TB, a8_tile32>(w, ctab, x8, dx, m, y, y_dt, stream);
         case 64: return a8_tile_dtypes<TB, a8_tile64>(w, ctab, x8, dx, m, y, y_dt, stream);
+        case 128: return a8_tile_dtypes<TB, a8_tile128>(w, ctab, x8, dx, m, y, y_dt, stream);
     }
     return hipErrorNotSupported;
 }
