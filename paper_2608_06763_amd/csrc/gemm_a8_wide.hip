@@ -6,7 +6,6 @@ namespace cq {
 
 bool gemm_a8_wide_supported(const cq_weight &w, int64_t m) {
     const int64_t lim = int64_t(1) << 31;
-    if (w.group != 32 && w.group != 64 && w.group != 128 && w.group != 256 && w.group != 512) return false;
     return m * w.k < lim && stream_fits(w.n, w.k, w.bits, w.group) && w.n < lim - 128 && m < lim - 256;
 }
 

@@ -23,6 +23,7 @@
 // 64..256-entry table per group would cost more than it saves).
 #include "cq_device.h"
 #include "cq_internal.h"
+#include "stream_common.h"
 
 namespace cq {
 
@@ -344,6 +345,7 @@ static hipError_t lut_bits(const cq_weight &w, const void *x, int64_t m, void *y
 }
 
 bool gemv_a16_lut_supported(const cq_weight &w, int64_t m) {
+    if (!group_instantiated(w.group)) return false;
     if (!(w.group <= 128 ? m <= 4 : (w.group == 256 && m <= 1))) return false;
     // the (R, MR) configuration lut_rows picks must fit 64 KB of LDS
     const int upg = w.group / 32;

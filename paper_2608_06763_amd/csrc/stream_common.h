@@ -107,11 +107,16 @@ __device__ __forceinline__ void store_row_pair(void *y, int row0, float v0, floa
     }
 }
 
-// Host check: every buffer a streaming kernel reads (codes, FP32 scales,
-// activations of up to 2 bytes) is addressable with 31-bit offsets.
+// Group sizes that the kernels are instantiated for: the powers of two from 32
+// to 512.  Any other multiple of 32 is the work of the conservative kernels.
+inline bool group_instantiated(int group) { return group >= 32 && group <= 512 && (group & (group - 1)) == 0; }
+
+// Host check of every kernel but the conservative ones: an instantiated group,
+// and every buffer it reads (codes, FP32 scales, activations of up to 2 bytes)
+// addressable with 31-bit offsets.
 inline bool stream_fits(int64_t n, int64_t k, int bits, int group) {
     const int64_t lim = int64_t(1) << 31;
-    return n * (k * bits / 8) < lim && n * (k / group) * 4 < lim && k * 2 < lim;
+    return group_instantiated(group) && n * (k * bits / 8) < lim && n * (k / group) * 4 < lim && k * 2 < lim;
 }
 
 template <int CTRL>

@@ -268,6 +268,20 @@ def test_builtin_rules(clean_table, bits, group, m, md, a8):
     assert cq.cq_family_supported(cq.CQ_PATH_A8, a8, d, m)
 
 
+# groups that are no power of two: only the conservative kernels take them
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("group", [96, 160, 480])
+@pytest.mark.parametrize("m", [1, 3, 8, 20, 40, 130])
+def test_builtin_rules_other_groups(clean_table, bits, group, m):
+    d = _fake(bits, group, 4096, 9600)
+    want = "gemv_generic" if m <= 16 else "gemm_tiled"
+    for path in (cq.CQ_PATH_MODEL_DTYPE, cq.CQ_PATH_A8):
+        assert cq.cq_select_query(path, d, m) == want
+        for family in cq.FAMILIES:
+            if family not in ("auto", "gemv_generic", "gemm_tiled"):
+                assert not cq.cq_family_supported(path, family, d, m), family
+
+
 @pytest.mark.parametrize("n,k,m,want", [
     (28672, 8192, 4, "gemm_slab_staged"), (28672, 4096, 16, "gemm_slab_staged"), (4096, 14336, 2, "gemm_slab_staged"),
     (6144, 4096, 4, "gemm_slab"), (4096, 4096, 8, "gemm_slab"), (28672, 8192, 1, "gemv_rows"),

@@ -271,3 +271,33 @@ def test_wide_a8_near_ties(torch_dev, bits, group):
             say("wide near ties", bits, group, f, m)
             y = cq.cq_gemm_a8_family(w, x8_t, dx_t, f, y_dtype=torch_dev.float32).cpu().numpy().astype(np.float64)
             assert np.array_equal(y, want), f
+
+
+# Groups that are no power of two, which the conservative kernels take at every
+# row count on both paths (K: an odd number of 64-code steps at 96 and 160).
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("group,k", [(96, 1152), (160, 1280), (480, 1920)])
+@pytest.mark.parametrize("m", [1, 8, 40, 130])
+def test_other_groups(torch_dev, bits, group, k, m):
+    import paper_2608_06763_amd as cq
+    from oracle import a8 as A8
+    n = 131
+    w, codes, scale, a, b = random_weight(990 + bits, n, k, bits, group)
+    wd = F.decode(codes, bits, group, scale, a, b)
+    for dtype in ("bf16", "fp16"):
+        xb, xv = act(991 + m, m, k, dtype)
+        x = torch_dev.from_numpy(xb.view(np.int16)).cuda().view(
+            torch_dev.bfloat16 if dtype == "bf16" else torch_dev.float16)
+        say("other groups", bits, group, k, m, dtype)
+        y = cq.cq_gemm_model_dtype(w, x, y_dtype=torch_dev.float32)
+        bound = whole_bound(xv, wd) if m <= 16 else model_dtype_bound(xv, wd, dtype)
+        assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - xv @ wd.T) <= bound)
+    xb, xv = act(992 + m, m, k)
+    x8_np, dx_np = A8.quantize_act(xv)
+    x8, dx = torch_dev.from_numpy(x8_np).cuda(), torch_dev.from_numpy(dx_np.astype(np.float32)).cuda()
+    ref, parts = A8.gemm_a8(x8_np, dx_np, codes, bits, group, scale, a, b)
+    say("other groups a8", bits, group, k, m)
+    y = cq.cq_gemm_a8(w, x8, dx, y_dtype=torch_dev.float32)
+    assert np.max(np.abs(y.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+    tab = cq.cq_build_carriers(w)
+    assert torch_dev.equal(cq.cq_gemm_a8_carriers(w, tab, x8, dx, y_dtype=torch_dev.float32), y)
