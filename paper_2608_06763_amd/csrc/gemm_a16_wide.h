@@ -390,9 +390,12 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
         uint32_t cw[2][2][CW];  // [block][unit of the step]
     };
     wslot ws[NB];
-    // metadata of the next group whose tables are built
-    float ms[2];
-    uint32_t ma[2], mb[2];
+    // metadata of the next group whose tables are built; G = 32: of the next four
+    // groups, lane block q holding group q, and of the current four.  (With one
+    // group at a time the lines of 128 rows' metadata left the L1 between the loads
+    // of one and the next: W3, 9216 x 15652 FP16, 104 rows 265 us, now 148.)
+    float ms[2], cs[2];
+    uint32_t ma[2], mb[2], cab[2];
     const int nsteps = (units + 1) >> 1;
 
     // codes of step st (units past the last repeat it)
@@ -405,6 +408,18 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
         }
     };
     auto load_meta = [&](int group) __attribute__((always_inline)) {
+        if constexpr (SPG == 0) {
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb) {
+                const uint32_t gi = goff[jb] + uint32_t(min(4 * group + q, ng - 1));
+                ms[jb] = load_f32(rs, gi * 4u);
+                if constexpr (B >= 3) {
+                    ma[jb] = load_u16(ra, gi * 2u);
+                    mb[jb] = load_u16(rb, gi * 2u);
+                }
+            }
+            return;
+        }
         const uint32_t g = __builtin_amdgcn_readfirstlane(min(group, ng - 1));
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) {
@@ -430,9 +445,32 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
     decoder_t<B, XDT> dec[2];
     uint32_t hi[2][2][4], lo[2][2][4];  // operands [phase parity][block]
 
-    // tables or coefficients of the next group, and the request for the one after
+    // tables or coefficients of the next group, and the request for the one after;
+    // G = 32: of group E of the current four, and where E is 0 the next four become
+    // current
     int next_group = 0;
-    auto build = [&]() __attribute__((always_inline)) {
+    auto build = [&](auto e_c) __attribute__((always_inline)) {
+        constexpr int E = decltype(e_c)::value;
+        if constexpr (SPG == 0) {
+            if constexpr (E == 0) {
+#pragma unroll
+                for (int jb = 0; jb < 2; ++jb) {
+                    cs[jb] = ms[jb];
+                    if constexpr (B >= 3) cab[jb] = ma[jb] | (mb[jb] << 16);
+                }
+                load_meta(++next_group);
+            }
+            auto from_block = [&](uint32_t w) __attribute__((always_inline)) -> uint32_t {
+                const uint32_t h = __builtin_amdgcn_permlane32_swap(w, w, false, false)[E >> 1];
+                return __builtin_amdgcn_permlane16_swap(h, h, false, false)[E & 1];
+            };
+#pragma unroll
+            for (int jb = 0; jb < 2; ++jb) {
+                const uint32_t ab = B >= 3 ? from_block(cab[jb]) : 0u;
+                dec[jb].build(__uint_as_float(from_block(__float_as_uint(cs[jb]))), ab & 0xffffu, ab >> 16, q);
+            }
+            return;
+        }
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) dec[jb].build(ms[jb], ma[jb], mb[jb], q);
         load_meta(++next_group);
@@ -493,7 +531,7 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
     load_meta(0);
     unroll<0, NB>([&](auto b_c) __attribute__((always_inline)) { load_w(decltype(b_c)::value, ws[decltype(b_c)::value]); });
     unroll<0, NB - 1>([&](auto b_c) __attribute__((always_inline)) { load_x(decltype(b_c)::value, xbuf(b_c)); });
-    build();
+    build(std::integral_constant<int, 0>{});
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) {
         uint32_t f0, f1;
@@ -523,7 +561,7 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
     constexpr int kAfter = NB == 2 ? 4 : 3 * 4 + 2 * NX;
     auto do_step = [&](int st, auto p_c) __attribute__((always_inline)) {
         constexpr int P = decltype(p_c)::value;
-        if constexpr (SPG == 0) build();
+        if constexpr (SPG == 0) build(std::integral_constant<int, (2 * P + 1) % 4>{});
         vmem_order();
         load_x(st + NB - 1, xbuf(std::integral_constant<int, P + NB - 1>{}));
         vmem_order();
@@ -531,12 +569,12 @@ __global__ void __launch_bounds__(256, 2) gemm_a16_wide(
         vmem_order();
         load_w(st + NB, ws[P]);
         vmem_order();
-        bool start = SPG <= 1 || (SPG == 2 && P % 2 == 1);
+        bool start = SPG == 1 || (SPG != 4 && P % 2 == 1);  // a request for metadata follows
         if constexpr (SPG == 4) {
             start = --group_left == 0;
             if (start) group_left = units_per_group >> 1;
         }
-        if (start) build();
+        if (start || SPG == 0) build(std::integral_constant<int, (2 * P + 2) % 4>{});
         vmem_order();
         phase(xbuf(p_c), ws[(P + 1) % NB], std::integral_constant<int, 1>{});
         if (NB == 2 && start) wait_loads<kAfter + kMeta>();
