@@ -55,7 +55,7 @@ hipError_t launch_gemm_a16_wide(const cq_weight &w, const void *x, int x_dt, int
                                 int tile_rows, hipStream_t stream);
 // Few rows with split K (gemm_a16_split.h); whole: FP32 weights in three operand
 // parts, m <= 16 and B >= 6.
-bool gemm_a16_split_whole_preferred(const cq_weight &w, int64_t m);
+bool gemm_a16_split_whole_preferred(const cq_weight &w, int x_dt, int64_t m);
 bool gemm_a16_split_preferred(const cq_weight &w, int64_t m);
 hipError_t launch_gemm_a16_split(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool whole,
                                  hipStream_t stream);

@@ -42,9 +42,24 @@ hipError_t parts_bits(const cq_weight &w, const void *x, int64_t m, void *y, int
 // Up to 16 rows, B >= 6, against the generic GEMV, whose time grows with m
 // (W8 G128, us, generic / split: 8192 x 8192 at 8 rows 80 / 37; 4096 x 4096 at
 // 2, 4, 8 rows 17 / 20, 20 / 20, 25 / 20; 2048 x 2048 at 4, 16 rows 11 / 13,
-// 17 / 13).
-bool gemm_a16_split_whole_preferred(const cq_weight &w, int64_t m) {
-    return w.bits >= 6 && m <= 16 && gemm_a16_wide_supported(w, m) && (m >= 12 || (m >= 5 && w.n * w.k >= (1 << 24)));
+// 17 / 13).  On few weight rows the split kernel leaves most units idle while
+// the generic one, a wave per row, is not slowed by its m: W6 11520 x 1678, 5
+// rows FP16 29 / 47, BF16 12288 x 1588 33 / 43; W8 8192 x 598 FP16, 12 rows 24 /
+// 38; but 8192 x 1228, 16 rows 51 / 36.  So the times of both are estimated, in
+// 0.01 us: the generic kernel goes over K in sweeps of 2048 codes, with 1024
+// rows in flight; a wave of the split kernel takes an eighth of K in steps of
+// 128 codes (FP16 activations as two parts), in rounds of 256 tiles.  (Fitted to
+// calls of 5-16 rows, K 1024-16384, N 512-32768: of 3650 on which the split kernel
+// ran 280 were more than 3% slower than the generic one, up to 1.6 times; with this
+// rule 7 of 4800, up to 1.07 times.)
+bool gemm_a16_split_whole_preferred(const cq_weight &w, int x_dt, int64_t m) {
+    if (w.bits < 6 || m < 5 || m > 16 || !gemm_a16_wide_supported(w, m)) return false;
+    if (m < 12 && w.n * w.k < (1 << 24)) return false;
+    const int64_t sweeps = (w.k + 2047) / 2048, waves = (w.n + 1023) / 1024;
+    const int64_t generic = 440 + sweeps * (90 + 35 * m + (waves - 1) * (98 + 13 * m));
+    const int64_t steps = ((w.k + 127) / 128 + kKS - 1) / kKS, rounds = split_rounds(w.n, m);
+    const int64_t split = 100 + rounds * 350 + steps * ((x_dt == 0 ? 320 : 380) + (rounds - 1) * 300);
+    return split < generic;
 }
 
 // More than 16 rows.  Every tile of 32 x 32 decodes its weights anew, which pays

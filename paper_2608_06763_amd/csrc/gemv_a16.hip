@@ -114,7 +114,7 @@ static hipError_t dispatch_bits(const cq_weight &w, const void *x, int64_t m, vo
 
 hipError_t launch_gemv_a16_generic(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
                                    hipStream_t stream) {
-    if (gemm_a16_split_whole_preferred(w, m)) return launch_gemm_a16_split(w, x, x_dt, m, y, y_dt, true, stream);
+    if (gemm_a16_split_whole_preferred(w, x_dt, m)) return launch_gemm_a16_split(w, x, x_dt, m, y, y_dt, true, stream);
     if (x_dt == 0) {
         if (y_dt == 0) return dispatch_bits<0, 0>(w, x, m, y, stream);
         return dispatch_bits<0, 2>(w, x, m, y, stream);
