@@ -145,8 +145,8 @@ __global__ void __launch_bounds__(64 * KS) gemm_a8_split(
             for (int jb = 0; jb < 2; ++jb) dec[jb].build(o.a[jb], o.b[jb]);
         }
         i32x4 op[2][2];  // [half of the unit][row block]
-        uint32_t tie = ~0u;
-        int kmin = 0;
+        uint32_t tie[2][2] = {{~0u, ~0u}, {~0u, ~0u}};
+        int kmin[2][2] = {{0, 0}, {0, 0}};
         uint32_t fw[2][2][window<B>::CW];
 #pragma unroll
         for (int jb = 0; jb < 2; ++jb) {
@@ -159,18 +159,23 @@ __global__ void __launch_bounds__(64 * KS) gemm_a8_split(
             for (int jb = 0; jb < 2; ++jb) {
                 uint32_t out[4];
                 unroll<0, 4>([&](auto t_c) __attribute__((always_inline)) {
-                    dec[jb].template quad<decltype(t_c)::value>(fw[kk][jb], out, tie, kmin);
+                    dec[jb].template quad<decltype(t_c)::value>(fw[kk][jb], out, tie[kk][jb], kmin[kk][jb]);
                 });
 #pragma unroll
                 for (int e = 0; e < 4; ++e) op[kk][jb][e] = int(out[e]);
             }
-        if (dec_t::kCheck && __builtin_expect(__any(tie <= 0x200u || kmin == -(1 << (B - 1))), 0)) {
+        auto call = [&](uint32_t t, int k) __attribute__((always_inline)) -> bool {
+            return __any(t <= 0x200u || k == -(1 << (B - 1)));
+        };
+        if (dec_t::kCheck && __builtin_expect(call(min(min(tie[0][0], tie[0][1]), min(tie[1][0], tie[1][1])),
+                                                   min(min(kmin[0][0], kmin[0][1]), min(kmin[1][0], kmin[1][1]))), 0)) {
 #pragma unroll
             for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
                 for (int jb = 0; jb < 2; ++jb) {
+                    if (!call(tie[kk][jb], kmin[kk][jb])) continue;
                     uint32_t out[4];
-                    dec_t::fix(fw[kk][jb], o.a[jb], o.b[jb], out);
+                    dec[jb].fix(fw[kk][jb], o.a[jb], o.b[jb], out);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) op[kk][jb][e] = int(out[e]);
                 }

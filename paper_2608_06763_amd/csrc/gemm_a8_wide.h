@@ -162,6 +162,21 @@ struct decoder {
             for (int i = 0; i < 4; ++i) tb[i] = (0x80808080u - tb[i]) ^ 0x80808080u;
         }
     }
+    // 127 q(|k|/M) sign(k) + 1.5 * 2^28 in FP64: the low word is the value in
+    // units of 2^-24, and its top byte, half a unit added, the rounded carrier.
+    // (FP64 multiply-adds issue at the FP32 rate here.)  The estimate's error is
+    // below 2^-44; a value within 2^-24 of a half-integer leaves a fraction of at
+    // most one unit.
+    __device__ __forceinline__ uint32_t estimate(int k, uint32_t &tie) const {
+        const double kd = double(k), ak = __builtin_fabs(kd);
+        const double v = __builtin_fma(kd, __builtin_fma(ak, __builtin_fma(ak, cc, cb), ca), 402653184.0);
+        const uint32_t r = uint32_t(__builtin_bit_cast(uint64_t, v)) + 0x00800000u;
+        tie = min(tie, (r << 8) + 0x100u);
+        return r;
+    }
+    static __device__ __forceinline__ uint32_t pack(const uint32_t (&r)[4]) {
+        return perm(perm(r[3], r[2], 0x0c0c0703u), perm(r[1], r[0], 0x0c0c0703u), 0x05040100u);
+    }
     // carriers of codes 4T .. 4T + 3 (aligned window f) into out[T]
     template <int T>
     __device__ __forceinline__ void quad(const uint32_t *f, uint32_t *out, uint32_t &tie, int &kmin) const {
@@ -187,48 +202,63 @@ struct decoder {
                 out[T] = perm(B == 3 ? tb[0] : 0u, ta[0], sel);
             }
         } else {
-            // 127 q(|k|/M) sign(k) + 1.5 * 2^28 in FP64: the low word is the
-            // value in units of 2^-24, and its top byte, half a unit added, the
-            // rounded carrier.  (FP64 multiply-adds issue at the FP32 rate here.)
-            // The estimate's error is below 2^-44; a value within 2^-24 of a
-            // half-integer leaves a fraction of at most one unit.
             uint32_t r[4];
             unroll<0, 4>([&](auto e_c) __attribute__((always_inline)) {
                 constexpr int E = decltype(e_c)::value;
                 const int k = field<B, 4 * T + E>(f);
                 kmin = min(kmin, k);
-                const double kd = double(k), ak = __builtin_fabs(kd);
-                const double v = __builtin_fma(kd, __builtin_fma(ak, __builtin_fma(ak, cc, cb), ca), 402653184.0);
-                r[E] = uint32_t(__builtin_bit_cast(uint64_t, v)) + 0x00800000u;
-                tie = min(tie, (r[E] << 8) + 0x100u);
+                r[E] = estimate(k, tie);
             });
-            out[T] = perm(perm(r[3], r[2], 0x0c0c0703u), perm(r[1], r[0], 0x0c0c0703u), 0x05040100u);
+            out[T] = pack(r);
         }
     }
-    // the sixteen carriers again, each by the exact test, the reserved pattern
-    // (never written by the packer) as 0
-    static __device__ __forceinline__ void fix(const uint32_t *f, uint32_t a16, uint32_t b16, uint32_t *out) {
+    // The sixteen carriers again from the same coefficients, the exact test for
+    // the few near a tie, the reserved pattern (never written by the packer) as 0.
+    // An exact tie needs q = 1/2, which W7 has at t = 2/3 in one group of 7000, and
+    // then in nearly every step of the group; with the exact test for all sixteen
+    // codes such a step took 10 us (2048 x 1198 W7 G512, 6 rows: 45 us, now 18).
+    __device__ __forceinline__ void fix(const uint32_t *f, uint32_t a16, uint32_t b16, uint32_t *out) const {
         if constexpr (kCheck) {
-            const float a = f16_to_f32(uint16_t(a16)), b = f16_to_f32(uint16_t(b16));
-            const float c = 1.f - a - b;
-            const float margin = carrier_margin(a, b, c);
             uint32_t w[4] = {f[0], window<B>::CW > 1 ? f[1] : 0u, window<B>::CW > 2 ? f[2] : 0u,
                              window<B>::CW > 3 ? f[3] : 0u};
             uint32_t o[4] = {0, 0, 0, 0};
 #pragma unroll 1
-            for (int j = 0; j < 16; ++j) {
-                int k = __builtin_amdgcn_sbfe(int(w[0]), 0, B);
-                if (k == -(1 << (B - 1))) k = 0;
-                const int mag = k < 0 ? -k : k;
-                const int cr = int(carrier_u8<M>(mag, float(mag) / float(M), a, b, c, margin));
-                const uint32_t byte = uint32_t(k < 0 ? -cr : cr) & 0xffu;
+            for (int t = 0; t < 4; ++t) {
+                uint32_t v = w[0], near = 0, r[4];
+                unroll<0, 4>([&](auto e_c) __attribute__((always_inline)) {
+                    constexpr int E = decltype(e_c)::value;
+                    int k = __builtin_amdgcn_sbfe(int(v), E * B, B);
+                    if (k == -(1 << (B - 1))) k = 0;
+                    uint32_t tie = ~0u;
+                    r[E] = estimate(k, tie);
+                    near |= tie <= 0x200u ? 1u << E : 0u;
+                });
+                uint32_t q4 = pack(r);
+                if (__any(near != 0)) {
+#pragma unroll 1
+                    for (int e = 0; e < 4; ++e) {
+                        if (__any(near & 1u)) {
+                            // the double arithmetic stays inside this branch
+                            uint32_t ea = a16, eb = b16;
+                            __asm__ volatile("" : "+v"(ea), "+v"(eb));
+                            int k = __builtin_amdgcn_sbfe(int(v), 0, B);
+                            if (k == -(1 << (B - 1))) k = 0;
+                            const int c = exact_carrier(k < 0 ? -k : k, M, double(f16_to_f32(uint16_t(ea))),
+                                                        double(f16_to_f32(uint16_t(eb))));
+                            q4 = (q4 & 0xffffff00u) | (uint32_t(k < 0 ? -c : c) & 0xffu);
+                        }
+                        q4 = __builtin_amdgcn_alignbit(q4, q4, 8);
+                        v >>= B;
+                        near >>= 1;
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], B);
-                    o[i] = __builtin_amdgcn_alignbit(o[i + 1], o[i], 8);
+                    w[i] = B == 8 ? w[i + 1] : __builtin_amdgcn_alignbit(w[i + 1], w[i], 4 * B & 31);
+                    o[i] = o[i + 1];
                 }
-                w[3] >>= B;
-                o[3] = (o[3] >> 8) | (byte << 24);
+                w[3] = B == 8 ? 0u : w[3] >> (4 * B & 31);
+                o[3] = q4;
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) out[i] = o[i];
@@ -504,7 +534,7 @@ __global__ void __launch_bounds__(256, 2) gemm_a8_wide(
                 for (int jb = 0; jb < 2; ++jb) {
                     uint32_t a = 0, b = 0, out[4];
                     shape_of(o, kk, jb, a, b);
-                    decoder<B, TB>::fix(fw[kk][jb], a, b, out);
+                    pick(kk, jb).fix(fw[kk][jb], a, b, out);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) op[P][kk][jb][e] = int(out[e]);
                 }
