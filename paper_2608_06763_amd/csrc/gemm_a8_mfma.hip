@@ -502,7 +502,8 @@ static hipError_t a8_mfma_dispatch(const cq_weight &w, const int8_t *ctab, const
 
 // x-tile height for m rows when the caller does not name one, 0 for the wide
 // kernel (at its own choice).  Up to 64 rows the tiles of gemm_a8_tile.hip
-// (28672 x 8192 W4, 64 rows: 92 us, the wide kernel 69 there).  Above, the wide
+// (28672 x 8192 W4, 64 rows: 92 us, the wide kernel 69 there; but at G = 64 101
+// and 146, 8640 x 22116, 48 rows).  Above, the wide
 // kernel and the tiles of 128 (up to 128 rows) and 256 rows, whose eight waves
 // hide more of their latency where there is one workgroup to a compute unit and
 // which decode a weight once for twice the rows at G != 128.  `over(h)`: the wide
@@ -520,7 +521,7 @@ static hipError_t a8_mfma_dispatch(const cq_weight &w, const int8_t *ctab, const
 //     165; three for two: 3072 x 8192, 1200 rows 75 / 88, 1024 x 8192 45 / 45
 static int a8_mfma_tile_rows(const cq_weight &w, int64_t m) {
     if (m <= 32) return 32;
-    if (m <= 64) return w.n > 16384 ? 0 : 64;
+    if (m <= 64) return w.n > 16384 && w.group != 64 ? 0 : 64;
     const int64_t tn = (w.n + 127) / 128;
     auto rounds = [&](int64_t h) { return ((m + h - 1) / h * tn + 255) / 256; };
     auto over = [&](int64_t h) { return rounds(h) > 1; };
