@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "cq_internal.h"
+#include "stream_common.h"
 
 namespace cq {
 
@@ -78,8 +79,9 @@ int default_family(int path, const cq_weight &w, int64_t m, int64_t gemv_max_row
         return gemm_a16_mfma_supported(w, m) ? CQ_FAMILY_GEMM_MFMA : CQ_FAMILY_GEMM_TILED;
     }
     // Dynamic A8: a partials dump is written by the generic GEMV, the W4
-    // matrix-core GEMM and the 64 x 64 GEMM only
-    if (gemv) {
+    // matrix-core GEMM and the 64 x 64 GEMM only; the GEMV's sums the units of a
+    // group over adjacent lanes, a power of two of them
+    if (gemv && !(partials && !group_instantiated(w.group))) {
         if (!partials && gemv_a8_stream_supported(w, m)) return CQ_FAMILY_GEMV_STREAM;
         if (!partials && gemv_a8_narrow_supported(w, m)) return CQ_FAMILY_GEMV_NARROW;
         return CQ_FAMILY_GEMV_GENERIC;

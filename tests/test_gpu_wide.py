@@ -308,3 +308,6 @@ def test_other_groups(torch_dev, bits, group, k, m):
     assert np.max(np.abs(y.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
     tab = cq.cq_build_carriers(w)
     assert torch_dev.equal(cq.cq_gemm_a8_carriers(w, tab, x8, dx, y_dtype=torch_dev.float32), y)
+    y, p = cq.cq_gemm_a8(w, x8, dx, y_dtype=torch_dev.float32, want_partials=True)
+    assert np.array_equal(p.cpu().numpy(), parts)
+    assert np.max(np.abs(y.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
