@@ -22,6 +22,15 @@ extern "C" {
  */
 cq_status cq_probe_read(const void *buf, int64_t bytes, uint32_t *sink, void *stream);
 
+/*
+ * cq_probe_wide_rows -- x-tile height (rows of x per workgroup tile) that the
+ * wide lane-decoded GEMM of a path (CQ_PATH_MODEL_DTYPE, CQ_PATH_A8) takes for m
+ * rows when the caller names none; 0 where that kernel does not take the call.
+ * Whether a call takes the kernel at all is another choice (cq.h).  Host only: a
+ * test states with it which heights its shapes run.
+ */
+int32_t cq_probe_wide_rows(int32_t path, const cq_weight *w, int64_t m);
+
 #ifdef __cplusplus
 }
 #endif

@@ -11,7 +11,8 @@ Entry points (same names as the C ABI):
   cq_gemm_routed_model_dtype, cq_gemm_routed_model_dtype_noalloc, cq_set_gemv_max_rows, cq_get_gemv_max_rows,
   cq_set_a8_fused_launch, cq_get_a8_fused_launch,
   cq_family_supported, cq_gemm_model_dtype_family, cq_gemm_a8_family,
-  cq_select_set, cq_select_query, cq_probe_read (measurement aid, include/cq_measure.h)
+  cq_select_set, cq_select_query, cq_probe_read and cq_probe_wide_rows (measurement aids,
+  include/cq_measure.h)
 The measured kernel-selection tuner that fills the selection table is in
 ``selection.py``.
 """
@@ -34,7 +35,7 @@ EXPORTS = ("cq_status_str", "cq_pack_groups", "cq_decode_ref", "cq_gemm_model_dt
            "cq_gemm_routed_model_dtype", "cq_set_gemv_max_rows", "cq_get_gemv_max_rows",
            "cq_family_supported", "cq_gemm_model_dtype_family", "cq_gemm_a8_family", "cq_select_set",
            "cq_select_query", "cq_probe_read", "cq_gemm_routed_model_dtype_noalloc", "cq_set_a8_fused_launch",
-           "cq_get_a8_fused_launch")
+           "cq_get_a8_fused_launch", "cq_probe_wide_rows")
 
 CQ_PATH_MODEL_DTYPE, CQ_PATH_A8 = 0, 1
 FAMILIES = {"auto": 0, "gemv_stream": 1, "gemv_lut": 2, "gemv_narrow": 3, "gemv_generic": 4, "gemm_mfma": 5,
@@ -117,6 +118,8 @@ def lib() -> ctypes.CDLL:
     L.cq_select_set.argtypes = [ctypes.POINTER(cq_select_entry), i64]
     L.cq_select_query.restype = ctypes.c_int
     L.cq_select_query.argtypes = [i32, ctypes.POINTER(cq_weight), ctypes.c_int, i64, ctypes.POINTER(i32)]
+    L.cq_probe_wide_rows.restype = i32
+    L.cq_probe_wide_rows.argtypes = [i32, ctypes.POINTER(cq_weight), i64]
     L.cq_probe_read.restype = ctypes.c_int
     L.cq_probe_read.argtypes = [vp, i64, vp, vp]
     _lib = L
@@ -438,3 +441,8 @@ def cq_probe_read(buf, sink, stream=None):
     ``sink`` is a one-element int32 device tensor."""
     _check(lib().cq_probe_read(buf.data_ptr(), buf.numel() * buf.element_size(), sink.data_ptr(), _stream_ptr(stream)),
            "cq_probe_read")
+
+
+def cq_probe_wide_rows(path: int, w, m: int) -> int:
+    """x-tile height that the wide GEMM of ``path`` takes for m rows (0: it does not take them)."""
+    return lib().cq_probe_wide_rows(path, ctypes.byref(w if isinstance(w, cq_weight) else w.desc), m)

@@ -350,6 +350,13 @@ cq_status cq_probe_read(const void *buf, int64_t bytes, uint32_t *sink, void *st
     return hip_status(cq::launch_read_probe(buf, bytes, sink, static_cast<hipStream_t>(stream)));
 }
 
+int32_t cq_probe_wide_rows(int32_t path, const cq_weight *w, int64_t m) {
+    if (check_weight(w) != CQ_OK || m < 1) return 0;
+    if (path == CQ_PATH_MODEL_DTYPE) return cq::gemm_a16_wide_supported(*w, m) ? cq::a16_wide_tile_rows(*w, m) : 0;
+    if (path == CQ_PATH_A8) return cq::gemm_a8_wide_supported(*w, m) ? cq::a8_wide_tile_rows(*w, m) : 0;
+    return 0;
+}
+
 cq_status cq_select_query(int32_t path, const cq_weight *w, cq_dtype x_dtype, int64_t m, int32_t *family) {
     const cq_status st = check_weight(w);
     if (st != CQ_OK) return st;

@@ -51,6 +51,7 @@ hipError_t launch_gemm_a16_mfma(const cq_weight &w, const void *x, int x_dt, int
 // Its tall tiles, every B and G a power of two from 32 to 512: tile_rows is 64,
 // 128, 160 or 256, 0 for the built-in choice by the shape.
 bool gemm_a16_wide_supported(const cq_weight &w, int64_t m);
+int a16_wide_tile_rows(const cq_weight &w, int64_t m);  // that choice
 hipError_t launch_gemm_a16_wide(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
                                 int tile_rows, hipStream_t stream);
 // Few rows with split K (gemm_a16_split.h); whole: FP32 weights in three operand
@@ -135,6 +136,7 @@ hipError_t launch_gemm_a8_mfma(const cq_weight &w, const int8_t *x8, const float
 // dump): tile_rows is 32, 64, 128 or 256, 0 for the built-in choice by the
 // shape; ctab (W3 and W4, G >= 64) may be null.
 bool gemm_a8_wide_supported(const cq_weight &w, int64_t m);
+int a8_wide_tile_rows(const cq_weight &w, int64_t m);  // that choice
 hipError_t launch_gemm_a8_wide(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
                                void *y, int y_dt, int tile_rows, hipStream_t stream);
 // Few rows with split K (gemm_a8_split.h).

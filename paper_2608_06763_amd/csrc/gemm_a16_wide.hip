@@ -15,7 +15,7 @@ bool gemm_a16_wide_supported(const cq_weight &w, int64_t m) {
 // unit take twice as long).  Measured, K = 4096, W4 G128, us by height
 // 64 / 128 / 160 / 256: N = 14336: 300 rows 173 / 131 / 86 / 109, 1024 rows
 // 404 / 269 / 283 / 197; N = 4096: 512 rows 70 / 77 / 82 / 101.
-static int wide_tile_rows(const cq_weight &w, int64_t m) {
+int a16_wide_tile_rows(const cq_weight &w, int64_t m) {
     const int64_t tn = (w.n + a16_wide::kTN - 1) / a16_wide::kTN;
     int best = 256;
     int64_t best_cost = INT64_MAX;
@@ -32,7 +32,7 @@ static int wide_tile_rows(const cq_weight &w, int64_t m) {
 
 hipError_t launch_gemm_a16_wide(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt,
                                 int tile_rows, hipStream_t stream) {
-    switch (tile_rows ? tile_rows : wide_tile_rows(w, m)) {
+    switch (tile_rows ? tile_rows : a16_wide_tile_rows(w, m)) {
         case 64: return launch_a16_wide64(w, x, x_dt, m, y, y_dt, stream);
         case 128: return launch_a16_wide128(w, x, x_dt, m, y, y_dt, stream);
         case 160: return launch_a16_wide160(w, x, x_dt, m, y, y_dt, stream);

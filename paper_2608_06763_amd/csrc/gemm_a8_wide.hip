@@ -18,7 +18,7 @@ static int max_rows(const cq_weight &w) {
 // compute unit at a time.  Measured, W4 G128, us at 64 / 128 / 256 rows:
 // 4096 x 4096, 100 rows: 36 / 47 / 64; 8192 x 28672, 8192 rows: 5296 / 3469 /
 // 2740.
-static int wide_tile_rows(const cq_weight &w, int64_t m) {
+int a8_wide_tile_rows(const cq_weight &w, int64_t m) {
     const int64_t tn = (w.n + a8_wide::kTN - 1) / a8_wide::kTN;
     int best = 64;
     int64_t best_cost = INT64_MAX;
@@ -37,7 +37,7 @@ static int wide_tile_rows(const cq_weight &w, int64_t m) {
 hipError_t launch_gemm_a8_wide(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
                                void *y, int y_dt, int tile_rows, hipStream_t stream) {
     if (tile_rows > max_rows(w)) tile_rows = max_rows(w);
-    switch (tile_rows ? tile_rows : wide_tile_rows(w, m)) {
+    switch (tile_rows ? tile_rows : a8_wide_tile_rows(w, m)) {
         case 32: return launch_a8_wide32(w, ctab, x8, dx, m, y, y_dt, stream);
         case 64: return launch_a8_wide64(w, ctab, x8, dx, m, y, y_dt, stream);
         case 128: return launch_a8_wide128(w, ctab, x8, dx, m, y, y_dt, stream);

@@ -268,6 +268,19 @@ def test_builtin_rules(clean_table, bits, group, m, md, a8):
     assert cq.cq_family_supported(cq.CQ_PATH_A8, a8, d, m)
 
 
+# x-tile heights that the shapes of the GPU tests stand for (131 weight rows
+# repeated): a change of the choice must not drop one of them unseen
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("group,k", [(32, 1152), (64, 1152), (128, 1152), (256, 1280), (512, 1536)])
+def test_wide_tile_heights(bits, group, k):
+    rows = lambda path, repeat, m: cq.cq_probe_wide_rows(path, _fake(bits, group, 131 * repeat, k), m)
+    for m, repeat, height in ((130, 1, 64), (100, 214, 128), (300, 104, 160), (450, 104, 256)):
+        assert rows(cq.CQ_PATH_MODEL_DTYPE, repeat, m) == height
+    most = 64 if group == 32 else 256 if group == 128 and bits <= 4 else 128
+    for m, repeat, height in ((17, 256, 32), (64, 128, 64), (130, 52, 64), (500, 104, 256)):
+        assert rows(cq.CQ_PATH_A8, repeat, m) == min(height, most)
+
+
 # groups that are no power of two: only the conservative kernels take them
 @pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("group", [96, 160, 480])

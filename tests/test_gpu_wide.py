@@ -57,18 +57,16 @@ def model_dtype_bound(xv, wd, dtype):
     return (per_weight + 2.0 ** -24 * np.sqrt(xv.shape[1]) * 4) * mass + 1e-30
 
 
-# m: one row block, a ragged tile of 64, 128 and (with many weight rows, where
-# the built-in height changes) 160 and 256 rows of x; K: several loop trips, an
+# m: one row block, a ragged tile of 64 and, with many weight rows, of 128, 160
+# and 256 rows of x (test_wide_tile_heights of test_abi_host.py); K: several loop trips, an
 # odd number of steps, an odd number of 32-code units where the width allows it
 @pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("group,k", [(32, 1152), (64, 1152), (128, 1152), (256, 1280), (512, 1536)])
-@pytest.mark.parametrize("m,repeat", [(17, 1), (130, 1), (300, 104), (450, 104)])
+@pytest.mark.parametrize("m,repeat", [(17, 1), (130, 1), (100, 214), (300, 104), (450, 104)])
 def test_wide_model_dtype(torch_dev, bits, group, k, m, repeat):
     import paper_2608_06763_amd as cq
     if group == 32 and bits in (4, 8):
         k = 1056
-    if repeat > 1 and group not in (32, 128):
-        pytest.skip("tall tiles are covered at two group sizes")
     n = 131
     w, codes, scale, a, b = random_weight(900 + bits, n, k, bits, group, repeat)
     wd = F.decode(codes, bits, group, scale, a, b)
@@ -126,15 +124,13 @@ def test_split_whole_precision(torch_dev, bits, group, dtype):
 # family), the many-row operands above; K of 17 and 33 steps of 128
 # codes over eight waves (some with one step more, the last with none or a part),
 # ragged weight and activation rows.
-@pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("group,k", [(32, 2176), (64, 2176), (128, 4224), (256, 2304), (512, 4608)])
-@pytest.mark.parametrize("m", [12, 16, 17, 33, 64, 130])
+@pytest.mark.parametrize("m,bits", [(m, bits) for m in (12, 16, 17, 33, 64, 130) for bits in range(1, 9)
+                                    if m > 32 or bits > 5])  # (else the slab kernels' rows)
 def test_split_model_dtype(torch_dev, bits, group, k, m):
     import paper_2608_06763_amd as cq
     if group == 32 and bits in (4, 8):
         k = 2080  # a step with one unit
-    if (m <= 16 or m <= 32) and bits <= 5:
-        pytest.skip("the slab kernels' rows")
     n = 75
     w, codes, scale, a, b = random_weight(980 + bits, n, k, bits, group)
     wd = F.decode(codes, bits, group, scale, a, b)
@@ -197,19 +193,17 @@ def test_few_rows_nonfinite(torch_dev, bits, dtype, group):
 # it) bit for bit, both rescale the exact INT32 partials in group order, and
 # against the oracle's semantics.  Heights of 32 to 256 rows, K ending inside a
 # step for the smaller groups, G above and below a step.
-@pytest.mark.parametrize("bits", range(1, 9))
-@pytest.mark.parametrize("group,k", [(32, 1152), (64, 1152), (64, 1216), (128, 1152), (256, 1280), (512, 1536)])
-@pytest.mark.parametrize("m,repeat", [(2, 1), (16, 1), (2, 62), (16, 8), (17, 1), (64, 1), (130, 1),
-                                      (17, 256), (64, 128), (130, 52), (500, 104)])
+# (rows are whole 16-byte units, and one long-group size runs the tall tiles)
+@pytest.mark.parametrize("bits,group,k,m,repeat", [
+    (bits, group, 1056 if group == 32 and bits in (4, 8) else k, m, repeat)  # 1056: an odd number of units
+    for bits in range(1, 9)
+    for group, k in [(32, 1152), (64, 1152), (64, 1216), (128, 1152), (256, 1280), (512, 1536)]
+    for m, repeat in [(2, 1), (16, 1), (2, 62), (16, 8), (17, 1), (64, 1), (130, 1),
+                      (17, 256), (64, 128), (130, 52), (500, 104)]
+    if (k * bits) % 128 == 0 and (repeat == 1 or group != 256)])
 def test_wide_a8(torch_dev, bits, group, k, m, repeat):
     import paper_2608_06763_amd as cq
     from oracle import a8 as A8
-    if group == 32 and bits in (4, 8):
-        k = 1056  # an odd number of units
-    if (k * bits) % 128:
-        pytest.skip("rows must be whole 16-byte units")
-    if repeat > 1 and group == 256:
-        pytest.skip("one long-group size at the tall tiles")
     n = 131
     w, codes, scale, a, b = random_weight(950 + bits, n, k, bits, group, repeat)
     xb, xv = act(951 + m, m, k)
@@ -261,13 +255,11 @@ def test_wide_a8(torch_dev, bits, group, k, m, repeat):
 
 # rows whose shapes put a carrier within 3e-4 of a half-integer: exact integer
 # sums from every kernel that forms carriers
-@pytest.mark.parametrize("bits", range(3, 9))
-@pytest.mark.parametrize("group", [32, 64, 128, 256])
+@pytest.mark.parametrize("bits,group", [(bits, group) for bits in range(3, 9) for group in (32, 64, 128, 256)
+                                        if (2 * group * bits) % 128 == 0])
 def test_wide_a8_near_ties(torch_dev, bits, group):
     import paper_2608_06763_amd as cq
     from tests._cases import carrier_probe
-    if (2 * group * bits) % 128:
-        pytest.skip("rows must be whole 16-byte units")
     codes, s, a, b, x8, dx, p = carrier_probe(bits, group)
     w = cq.CQWeight.from_codes(codes, s, a, b, bits, group)
     for m in (20, 70, 32970):  # split K, and more tiles than it takes
