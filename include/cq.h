@@ -213,12 +213,15 @@ cq_status cq_build_carriers(const cq_weight *w, int8_t *carriers, void *stream);
 /*
  * cq_gemm_a8_carriers -- Dynamic-A8 product with load-time carriers (device).
  *
- * Same result as cq_gemm_a8 (without the partials dump), bit for bit: the
- * kernels read the carriers of cq_build_carriers for the same weight instead
- * of forming them (the many-row W4 matrix-core GEMM and the generic kernels
- * of the other widths; the single-row kernels and the W3/W4 narrow-row
- * kernels, up to 32 rows, keep their register decode, which gives the same
- * carriers).
+ * Same result as cq_gemm_a8 (without the partials dump), bit for bit.  The
+ * carriers of cq_build_carriers for the same weight are read instead of formed
+ * by the many-row matrix-core GEMMs of W3 and W4 with G >= 64 (more than 32
+ * rows) and by the conservative kernels (the generic GEMV where the built-in
+ * rules keep it up to 16 rows, groups that are no power of two, tensors of
+ * 2 GiB and more).  All other kernels form the same carriers in registers and
+ * do not read the table: a single row, W3/W4 up to 32 rows, split K, and the
+ * wide kernels of the other widths and of G = 32.  So with W5-W8 the table, up
+ * to a byte per weight, is seldom worth keeping.
  *   carriers  the table of cq_build_carriers (NULL allowed for W1).
  * Errors as cq_gemm_a8.
  */
@@ -311,15 +314,18 @@ int64_t cq_get_gemv_max_rows(int32_t path);
  *   GEMV_NARROW   matrix-core narrow-row GEMV (model dtype 2 <= m <= 16,
  *                 B <= 5; A8 2 <= m <= 32, W3 and W4 with G >= 64, two
  *                 16-row blocks of x per decoded operand above 16 rows)
+ * GEMV_GENERIC and GEMM_TILED take every group; the others those that are a
+ * power of two.
  *   GEMV_GENERIC  conservative one-wave-per-row GEMV (m <= 16, every B, G);
  *                 without a partials dump the split-K matrix-core kernels
- *                 take the row counts on which they are faster
+ *                 take the calls on which they are faster (model dtype B >= 6
+ *                 from 5 rows; A8 from 2 rows, but not W3/W4 with G >= 64)
  *   GEMM_MFMA     tiled matrix-core GEMM (model dtype B <= 5; A8 W3/W4 with
  *                 G >= 64)
  *   GEMM_TILED    conservative tiled GEMM (every B, G): 64 x 64 tiles; A8
  *                 without a partials dump and model dtype B >= 6 run the wide
  *                 lane-decoded kernels, or split K over few tiles, where
- *                 their 32-bit offsets reach
+ *                 their 32-bit offsets reach and the group is a power of two
  *   GEMM_MFMA_ROUNDED  model dtype only: the tiled matrix-core GEMM with the
  *                 decoded weight s_g q rounded once to the activation dtype
  *                 before the dot, the dense rounding point of Sec. 5.3 (BF16:

@@ -133,12 +133,12 @@ bool gemm_a8_mfma_supported(const cq_weight &w, int64_t m);
 hipError_t launch_gemm_a8_mfma(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y, int y_dt,
                                int32_t *partials, int tile_rows, hipStream_t stream);
 // Its tall tiles and every B and G a power of two from 32 to 512 (no partials
-// dump): tile_rows is 32, 64, 128 or 256, 0 for the built-in choice by the
-// shape; ctab (W3 and W4, G >= 64) may be null.
+// dump), at the height a8_wide_tile_rows chooses by the shape (32, 64, 128 or
+// 256); ctab (W3 and W4, G >= 64) may be null.
 bool gemm_a8_wide_supported(const cq_weight &w, int64_t m);
-int a8_wide_tile_rows(const cq_weight &w, int64_t m);  // that choice
+int a8_wide_tile_rows(const cq_weight &w, int64_t m);
 hipError_t launch_gemm_a8_wide(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
-                               void *y, int y_dt, int tile_rows, hipStream_t stream);
+                               void *y, int y_dt, hipStream_t stream);
 // Few rows with split K (gemm_a8_split.h).
 bool gemm_a8_split_preferred(const cq_weight &w, int64_t m);
 hipError_t launch_gemm_a8_split(const cq_weight &w, const int8_t *x8, const float *dx, int64_t m, void *y, int y_dt,

@@ -19,9 +19,13 @@
 // of 1024 MFMA cycles per 32 codes at 64 x 64 per wave) than matrix time.  Here
 // the LDS carries only activations: 512 + 128 cycles per 1024 MFMA cycles.
 //
-// What bounds it: instruction issue.  Per 32 codes a wave issues 64 MFMAs
-// (1024 cycles) and about 90 (W4) to 180 (W6..W8) decode instructions of 4
-// cycles, two waves per SIMD.  Measured at 8192 x 10240, W4 G128, 2048 rows
+// What bounds it.  Per 32 codes a wave issues 64 MFMAs (1024 cycles) and about 90
+// (W4) to 180 (W6..W8) decode instructions of 4 cycles.  With two tiles to a
+// compute unit (two waves per SIMD) that is mostly the matrix cores: W4 at 8192 x
+// 10240, 2048 rows keeps them 54% busy, the VALU 33%, 12% of the time both.  A grid
+// of at most one tile per unit has one wave per SIMD, whose load latency and
+// barriers nothing hides: 4096 x 14336 W6, 512 rows 36% and 31%, 5120 x 13824 W3
+// FP16, 300 rows (two activation buffers) 16% and 18%.  Measured at 8192 x 10240, W4 G128, 2048 rows
 // (343 GFLOP): 571 us (602 TFLOP/s, twice that in MFMAs) against 791 for the
 // LDS-staged kernel; 438 without the decode, 384 without loads too, 359 for the
 // MFMAs alone.  4096 x 14336, W6 G128, 512 rows: 125 us against 651 for the

@@ -223,7 +223,7 @@ hipError_t launch_gemm_a8_tiled(const cq_weight &w, const int8_t *x8, const floa
     // this kernel keeps the partials dump and the tensors and groups the wide
     // kernel does not take (4096 x 14336 at 1024 rows, W8 G128: 2640 -> 250 us)
     if (!partials && gemm_a8_split_preferred(w, m)) return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
-    if (!partials && gemm_a8_wide_supported(w, m)) return launch_gemm_a8_wide(w, nullptr, x8, dx, m, y, y_dt, 0, stream);
+    if (!partials && gemm_a8_wide_supported(w, m)) return launch_gemm_a8_wide(w, nullptr, x8, dx, m, y, y_dt, stream);
     if (y_dt == 0) return dispatch_bits<0>(w, x8, dx, m, y, partials, nullptr, stream);
     if (y_dt == 1) return dispatch_bits<1>(w, x8, dx, m, y, partials, nullptr, stream);
     return dispatch_bits<2>(w, x8, dx, m, y, partials, nullptr, stream);

@@ -460,8 +460,8 @@ static hipError_t a8_mfma_group(const cq_weight &w, const int8_t *x8, const floa
     // The partials dump (a test path) runs four waves per workgroup, which
     // leaves room for its extra registers; the fast path runs eight.
     if (partials) {
-        if constexpr (B != 4) {
-            return hipErrorNotSupported;  // W3 partials: the 64x64 kernel
+        if constexpr (B != 4 || TB) {
+            return hipErrorNotSupported;  // W3 partials: the 64x64 kernel; tables: no dump
         } else {
         switch (w.group) {
             case 64: return a8_mfma_launch<B, 2, 2, 2, YDT, true, TB>(w, x8, dx, m, y, partials, ctab, stream);
@@ -541,7 +541,7 @@ static hipError_t a8_mfma_rows(const cq_weight &w, const int8_t *ctab, const int
     if (tile_rows == 0 && m > 32 && gemm_a8_split_preferred(w, m))
         return launch_gemm_a8_split(w, x8, dx, m, y, y_dt, stream);
     const int tr = tile_rows ? tile_rows : a8_mfma_tile_rows(w, m);
-    if (tr == 0) return launch_gemm_a8_wide(w, ctab, x8, dx, m, y, y_dt, 0, stream);
+    if (tr == 0) return launch_gemm_a8_wide(w, ctab, x8, dx, m, y, y_dt, stream);
     if (tr < 256) return launch_gemm_a8_tile(w, ctab, x8, dx, m, y, y_dt, tr, stream);
     if (ctab) return a8_mfma_dispatch<true>(w, ctab, x8, dx, m, y, y_dt, nullptr, stream);
     return a8_mfma_dispatch<false>(w, nullptr, x8, dx, m, y, y_dt, nullptr, stream);

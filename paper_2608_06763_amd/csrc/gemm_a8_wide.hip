@@ -35,9 +35,8 @@ int a8_wide_tile_rows(const cq_weight &w, int64_t m) {
 }
 
 hipError_t launch_gemm_a8_wide(const cq_weight &w, const int8_t *ctab, const int8_t *x8, const float *dx, int64_t m,
-                               void *y, int y_dt, int tile_rows, hipStream_t stream) {
-    if (tile_rows > max_rows(w)) tile_rows = max_rows(w);
-    switch (tile_rows ? tile_rows : a8_wide_tile_rows(w, m)) {
+                               void *y, int y_dt, hipStream_t stream) {
+    switch (a8_wide_tile_rows(w, m)) {
         case 32: return launch_a8_wide32(w, ctab, x8, dx, m, y, y_dt, stream);
         case 64: return launch_a8_wide64(w, ctab, x8, dx, m, y, y_dt, stream);
         case 128: return launch_a8_wide128(w, ctab, x8, dx, m, y, y_dt, stream);
