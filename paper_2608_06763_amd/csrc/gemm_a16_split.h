@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(64 * KS, PARTS == 3 ? 4 : 1) gemm_a16_split(
         const float sg = PARTS == 3 && (st & 1) ? -1.f : 1.f;
         decoder_t<B, WDT> d[2];
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb) d[jb].template build<G128>(in ? sg * o.s[jb] : 0.f, o.a[jb], o.b[jb], q);
+        for (int jb = 0; jb < 2; ++jb) d[jb].template build<G128, PARTS == 3>(in ? sg * o.s[jb] : 0.f, o.a[jb], o.b[jb], q);
         f32x4_t sum[2], half[2];  // PARTS == 3: chains' sums of this step
         unroll<0, 4>([&](auto c_c) __attribute__((always_inline)) {
             constexpr int C = decltype(c_c)::value;

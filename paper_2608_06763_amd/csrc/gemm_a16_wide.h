@@ -138,7 +138,8 @@ template <int B, int XDT>
 struct curve_decoder {
     float s, a, b, c;
 
-    template <bool SHARE = true>
+    // ONCE: for weights carried whole
+    template <bool SHARE = true, bool ONCE = false>
     __device__ __forceinline__ void build(float sv, uint32_t a16, uint32_t b16, int q) {
         const float av = f16_to_f32(uint16_t(a16)), bv = f16_to_f32(uint16_t(b16));
         const float cv = 1.f - av - bv;
@@ -148,14 +149,22 @@ struct curve_decoder {
             b = bv;
             c = cv;
         } else {
-            // s and the powers of 1/M folded into the coefficients, each rounded
-            // once: a formed weight is within 0.7 units of 2^-24 (rms), 0.8 for a
-            // correctly rounded k/M in the Horner form and 1.0 to 1.2 with a
-            // rounding for every factor
+            // s and the powers of 1/M folded into the coefficients.  With one
+            // rounding for each (ONCE) a formed weight is within 0.7 units of 2^-24
+            // (rms), 0.8 for a correctly rounded k/M in the Horner form; with one
+            // for every factor 1.0 to 1.2, which operands of hi + lo (2^-18) or FP16
+            // do not show and which costs less (4096 x 14336 W6, 512 rows: 1%)
             constexpr int M = max_code(B);
-            a = folded<M>(sv, av);
-            b = folded<M * M>(sv, bv);
-            c = folded<M * M * M>(sv, cv);
+            if constexpr (ONCE) {
+                a = folded<M>(sv, av);
+                b = folded<M * M>(sv, bv);
+                c = folded<M * M * M>(sv, cv);
+            } else {
+                constexpr float m = float(M);
+                a = sv * av * (1.f / m);
+                b = sv * bv * (1.f / (m * m));
+                c = sv * cv * (1.f / (m * m * m));
+            }
         }
     }
     // s v / D with one rounding (up to a remainder of 2^-46): the quotient's
@@ -215,7 +224,7 @@ struct table_decoder {
 
     // SHARE: the four lanes of a row (q = 0..3) form the tables of one group
     // together; without it every lane forms its own
-    template <bool SHARE = true>
+    template <bool SHARE = true, bool ONCE = false>
     __device__ __forceinline__ void build(float s, uint32_t a16, uint32_t b16, int q) {
         if constexpr (B <= 2) {
             uint32_t h, l;
