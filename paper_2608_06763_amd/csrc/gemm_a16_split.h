@@ -29,9 +29,10 @@
 //
 // What bounds it: VALU issue of the decode (W8 in three parts about 12
 // instructions a code: 8192 x 8192 needs 20 us of it on every SIMD) and its
-// latency at two waves per SIMD (VALU 53% busy, matrix cores 6%).  Measured: 8192 x 8192 W8 G128, 8 rows 37 us
-// (80 for one wave per weight row); K in 64-code steps with 8 codes per lane and
-// unit 41; 16 waves 39.  4096 x 4096 W4, 48 rows 19 us (55 for 64-row tiles);
+// latency at two waves per SIMD (VALU 53% busy, matrix cores 6%).
+// Measured: 8192 x 8192 W8 G128, 8 rows 34 us (80 for one wave per weight row); with
+// one chain of matrix instructions 32, then with K in 64-code steps with 8 codes
+// per lane and unit, or with 16 waves, 2 to 4 more.  4096 x 4096 W4, 48 rows 19 us (55 for 64-row tiles);
 // 14336 x 4096, 64 rows 46 (184); 4096 x 4096 W4, 128 rows 38 (63 for the wide
 // kernel).
 #pragma once
