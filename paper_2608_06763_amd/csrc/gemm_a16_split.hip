@@ -69,13 +69,14 @@ bool gemm_a16_split_whole_preferred(const cq_weight &w, int x_dt, int64_t m) {
 // W3 G64, 256 rows 151 / 31; 4096 x 2048 W8, 128 rows 73 / 25.  Two: 4096 x 4096
 // W4, 128 rows 63 / 38; 2048 x 8192, 64 rows 30 / 26, but W5 34 / 35 (3072 x
 // 8192: 50 / 42).  Three: 4096 x 4096, 192 rows W4 64 / 54, W8 75 / 69; 4096 x
-// 20000 W8, 20 rows 78 / 66; but 2048 x 4096 W3, 192 rows 35 / 39.  Four: 4096 x
+// 20000 W8, 20 rows 78 / 66; but 2048 x 4096 W3, 192 rows 35 / 39, and W5 6656 x
+// 12159 G256, 47 rows 78 / 88 (8832 x 8560 G128, 51 rows 126 / 118).  Four: 4096 x
 // 4096 W4, 256 rows 65 / 71.  Below K = 2048 a wave has fewer than two steps.
 bool gemm_a16_split_preferred(const cq_weight &w, int64_t m) {
     if (!gemm_a16_wide_supported(w, m)) return false;
     const int64_t rounds = split_rounds(w.n, m);
     if (rounds > 3) return false;
-    return w.k >= (rounds == 3 ? 4096 : rounds == 2 && w.bits == 5 ? 3072 : 2048);
+    return w.k >= (rounds == 3 ? (w.bits == 5 && m <= 64 ? 8192 : 4096) : rounds == 2 && w.bits == 5 ? 3072 : 2048);
 }
 
 hipError_t launch_gemm_a16_split(const cq_weight &w, const void *x, int x_dt, int64_t m, void *y, int y_dt, bool whole,

@@ -39,25 +39,29 @@ hipError_t split_bits(const cq_weight &w, const int8_t *x8, const float *dx, int
 }  // namespace
 
 // Up to 16 rows against the generic GEMV, whose time grows with m.  On few rows
-// and few weight rows the split kernel leaves units idle (generic / here, us: W7 G512 2048 x 1198, 3 rows 12 / 18; W2 G32 3584 x 1397, 2
-// rows 6 / 10; W8 G32 2048 x 1874, 2 rows 10 / 13).  Both times in 0.01 us: the
+// and few weight rows the split kernel leaves units idle (generic / here, us: W7
+// G512 2048 x 1198, 3 rows 12 / 18; W2 G32 3584 x 1397, 2 rows 6 / 10; W8 G32 2048 x 1874, 2 rows 10 / 13).  Both times in 0.01 us: the
 // generic kernel goes over K in sweeps of 2048 codes, 1024 weight rows in flight;
 // a wave here takes an eighth of K in whole groups, in steps of 128 codes with
-// tables per group, in rounds of 256 tiles.  Fitted to 2-16 rows, K 1024-16384, N 512-32768: of 4500 calls 237 were
-// more than 3% slower than the generic kernel, up to 1.9 times, with this rule 54,
-// up to 1.3 times.  W3 and W4 with G = 32 never were.
+// tables per group (and four rescales a step at G = 32), in rounds of 256 tiles.
+// Fitted to
+// 2-16 rows, K 1024-16384, N 512-32768: of 4500 calls 237 were more than 3% slower
+// than the generic kernel, up to 1.9 times; with this rule 64 of 9000, up to 1.26
+// times.  W3 and W4 with G = 32 never were.
 static bool few_rows_faster(const cq_weight &w, int64_t m) {
     const int64_t sweeps = (w.k + 2047) / 2048, waves = (w.n + 1023) / 1024;
     const int64_t chunk = w.group > 128 ? w.group / 128 : 1, all = (w.k + 127) / 128;
     const int64_t tables = ((all + chunk - 1) / chunk + kKS - 1) / kKS, steps = tables * chunk;
     const int64_t more = (w.n + 8191) / 8192 - 1;  // rounds after the first
-    if (w.bits <= 2)
-        return 430 + steps * 65 + tables * 30 + more * (20 + 90 * steps) <
-               430 + sweeps * ((w.bits == 1 ? 22 : 26) * m + (waves - 1) * (25 + 8 * m));
+    if (w.bits == 1 || w.bits == 2) {
+        const int64_t step = w.group == 32 ? 140 : w.group == 64 ? 105 : 100;
+        const int64_t sweep = w.bits == 1 ? 22 * m + (waves - 1) * (10 + 8 * m) : 26 * m + (waves - 1) * (35 + 7 * m);
+        return steps * step + more * (20 + 90 * steps) < sweeps * sweep;
+    }
     if (w.bits <= 4) return true;
     const int64_t generic = 620 + sweeps * (330 + 25 * m + (waves - 1) * (143 + 13 * m));
     if (w.bits == 5) return 430 + steps * 90 + tables * 225 + more * 195 * steps < generic;
-    return 475 + steps * 205 + tables * 85 + more * (100 + 290 * steps) < generic;
+    return 475 + steps * (w.group == 32 ? 305 : 205) + tables * 85 + more * (100 + 290 * steps) < generic;
 }
 
 // W3 and W4 with G >= 64 have the narrow kernel up to 32 rows (14336 x 4096 W4
