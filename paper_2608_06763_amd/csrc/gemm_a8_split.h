@@ -105,15 +105,6 @@ __global__ void __launch_bounds__(64 * KS) gemm_a8_split(
         for (int t = 0; t < NX; ++t) load_lds16(rx, buf + 1024 * t, xoff[t]);
     };
 
-    // row factors of the outputs, requested here so that no store waits for one
-    const auto rd = make_rsrc(dx, uint32_t(m) * 4u);
-    float f[BI][4];
-#pragma unroll
-    for (int i = 0; i < BI; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) f[i][r] = load_f32(rd, uint32_t(m0 + 16 * i + 4 * q + r) * 4u);
-    vmem_order();
-
     const i32x4 zero = {0, 0, 0, 0};
     f32x4 accf[BI][2];
     i32x4 part[GM == 0 ? BI : 1][2];  // INT32 partials of groups longer than a step
@@ -176,7 +167,7 @@ __global__ void __launch_bounds__(64 * KS) gemm_a8_split(
                 for (int jb = 0; jb < 2; ++jb) {
                     if (!call(tie[kk][jb], kmin[kk][jb])) continue;
                     uint32_t out[4];
-                    dec[jb].fix(fw[kk][jb], o.a[jb], o.b[jb], out);
+                    dec_t::fix(fw[kk][jb], o.a[jb], o.b[jb], out);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) op[kk][jb][e] = int(out[e]);
                 }
@@ -267,6 +258,18 @@ __global__ void __launch_bounds__(64 * KS) gemm_a8_split(
         }
     }
     wait_loads<0>();
+
+    // row factors of the outputs, requested here so that no store waits for one
+    // (before the K loop they took its registers: W4 G32 2560 x 5023, 62 rows 26 ->
+    // 29 us)
+    vmem_order();
+    const auto rd = make_rsrc(dx, uint32_t(m) * 4u);
+    float f[BI][4];
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f[i][r] = load_f32(rd, uint32_t(m0 + 16 * i + 4 * q + r) * 4u);
+    vmem_order();
     __syncthreads();
 
     // the waves' sums meet in the first activation buffer, as in

@@ -218,8 +218,15 @@ struct decoder {
     // An exact tie needs q = 1/2, which W7 has at t = 2/3 in one group of 7000, and
     // then in nearly every step of the group; with the exact test for all sixteen
     // codes such a step took 10 us (2048 x 1198 W7 G512, 6 rows: 45 us, now 18).
-    __device__ __forceinline__ void fix(const uint32_t *f, uint32_t a16, uint32_t b16, uint32_t *out) const {
+    // (The coefficients are formed anew, from opaque copies of the shape: with the
+    // decoder's own, kept alive for this branch, the kernels that spill spilled more,
+    // 14464 x 4852 W8 G32, 1503 rows 2270 -> 2660 us.)
+    static __device__ __forceinline__ void fix(const uint32_t *f, uint32_t a16, uint32_t b16, uint32_t *out) {
         if constexpr (kCheck) {
+            decoder d;
+            uint32_t shape[2] = {a16, b16};
+            __asm__ volatile("" : "+v"(shape[0]), "+v"(shape[1]));
+            d.set(shape);
             uint32_t w[4] = {f[0], window<B>::CW > 1 ? f[1] : 0u, window<B>::CW > 2 ? f[2] : 0u,
                              window<B>::CW > 3 ? f[3] : 0u};
             uint32_t o[4] = {0, 0, 0, 0};
@@ -231,7 +238,7 @@ struct decoder {
                     int k = __builtin_amdgcn_sbfe(int(v), E * B, B);
                     if (k == -(1 << (B - 1))) k = 0;
                     uint32_t tie = ~0u;
-                    r[E] = estimate(k, tie);
+                    r[E] = d.estimate(k, tie);
                     near |= tie <= 0x200u ? 1u << E : 0u;
                 });
                 uint32_t q4 = pack(r);
@@ -240,7 +247,7 @@ struct decoder {
                     for (int e = 0; e < 4; ++e) {
                         if (__any(near & 1u)) {
                             // the double arithmetic stays inside this branch
-                            uint32_t ea = a16, eb = b16;
+                            uint32_t ea = shape[0], eb = shape[1];
                             __asm__ volatile("" : "+v"(ea), "+v"(eb));
                             int k = __builtin_amdgcn_sbfe(int(v), 0, B);
                             if (k == -(1 << (B - 1))) k = 0;
@@ -535,7 +542,7 @@ __global__ void __launch_bounds__(256, 2) gemm_a8_wide(
                 for (int jb = 0; jb < 2; ++jb) {
                     uint32_t a = 0, b = 0, out[4];
                     shape_of(o, kk, jb, a, b);
-                    pick(kk, jb).fix(fw[kk][jb], a, b, out);
+                    decoder<B, TB>::fix(fw[kk][jb], a, b, out);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) op[P][kk][jb][e] = int(out[e]);
                 }
